@@ -126,8 +126,9 @@ typedef struct {
  * INT-1 value (+1, -1), and every partial sum is an integer below 2^24, so
  * the fp32 accumulator and hence the output equal the integer paths' bit for
  * bit, at twice the int8 matrix-core rate per instruction.  INT-1 layers take
- * QNN_EPI_THRESH1 or QNN_EPI_RAW32 as on the XNOR path.  The library never
- * picks this path by itself. */
+ * QNN_EPI_THRESH1 or QNN_EPI_RAW32 as on the XNOR path.  This value forces
+ * the tile kernel's e2m1 mode; the kernel that the library picks by itself
+ * for general layers uses the same instruction at 2 and 1 bits. */
 #define QNN_TILE_FP4 4
 /* Small images, a workgroup keeping whole padded images in local memory and
  * its filters in registers: stride 1, 3x3 or 5x5 filters, output rows of at

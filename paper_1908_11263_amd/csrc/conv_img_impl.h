@@ -408,19 +408,6 @@ __device__ __forceinline__ uint32_t stair_tree(int32_t acc, const int32_t *T)
 // read 32 consecutive words, one per bank), at the index the bits decided so
 // far give: for 15 thresholds the code is built one bit per comparison and
 // only T[3], T[7] and T[11] are held in registers.
-// 2 x + (acc >= t): the comparison's result is the carry into the add (two
-// instructions; written out because the compiler builds the bit with a select
-// and an or).  Only vcc, a vector-written lane mask, is clobbered.
-__device__ __forceinline__ uint32_t stair_bit(uint32_t x, int32_t acc, int32_t t)
-{
-    uint32_t r;
-    __asm__("v_cmp_ge_i32_e32 vcc, %1, %2\n\tv_addc_co_u32_e32 %0, vcc, %3, %3, vcc"
-            : "=v"(r)
-            : "v"(acc), "v"(t), "v"(x)
-            : "vcc");
-    return r;
-}
-
 template <int NT>
 __device__ __forceinline__ uint32_t stair_tree_col(int32_t acc, const int32_t *T, const int32_t *col)
 {

@@ -253,6 +253,19 @@ __device__ __forceinline__ uint32_t stair_level(int32_t acc, const int32_t *T)
     return code;
 }
 
+// 2 x + (acc >= t): the comparison's result is the carry into the add (two
+// instructions; written out because the compiler builds the bit with a select
+// and an or).  Only vcc, a vector-written lane mask, is clobbered.
+__device__ __forceinline__ uint32_t stair_bit(uint32_t x, int32_t acc, int32_t t)
+{
+    uint32_t r;
+    __asm__("v_cmp_ge_i32_e32 vcc, %1, %2\n\tv_addc_co_u32_e32 %0, vcc, %3, %3, vcc"
+            : "=v"(r)
+            : "v"(acc), "v"(t), "v"(x)
+            : "vcc");
+    return r;
+}
+
 // One batch of U packed-input quads of a tile: issue the loads ...
 // (F4: INT-2 codes staged as e2m1 nibbles, 4 bits per code, instead of bytes)
 template <int BITS, bool Q16, int U, int NT = 256, bool F4 = false>

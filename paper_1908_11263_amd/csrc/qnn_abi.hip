@@ -547,6 +547,204 @@ bool plan_img(ImgArgs &p, const qnn_tensor *x, int32_t m, const qnn_conv_geom *g
     return true;
 }
 
+// Streaming kernel (conv_stream_kernel): fills everything but the pointers;
+// false when the layer's offsets or tiles are out of its range.  Any filter,
+// stride and padding; a filter over the whole image and pointwise layers run
+// as one-pixel images (a plain matrix product).
+struct StreamTile {
+    int wm, wn, wch;
+    bool tail;  // built for narrow and odd pixels too
+};
+#define QNN_STREAM_HAS(V_, WM_, WN_, WCH_) v == V_ ||
+constexpr bool stream_tail_built(int v) { return QNN_STREAM_VARIANTS_TAIL(QNN_STREAM_HAS) false; }
+#define QNN_STREAM_TILE(V_, WM_, WN_, WCH_) {WM_, WN_, WCH_, stream_tail_built(V_)},
+constexpr StreamTile kStreamTiles[] = {QNN_STREAM_VARIANTS(QNN_STREAM_TILE)};
+#undef QNN_STREAM_TILE
+#undef QNN_STREAM_HAS
+
+bool plan_stream(StreamArgs &best, int &variant, const qnn_tensor *x, int32_t m, const qnn_conv_geom *g,
+                 const qnn_epi *e, int32_t ho, int32_t wo, bool pool)
+{
+    const int bits = x->bits;
+    const bool f4 = bits <= 2;
+    const int rb = f4 ? 16 * bits : 8 * bits;  // packed bytes of a 64-byte staged block
+    // e2m1 accumulators hold integers below 2^24 exactly
+    if (f4 && (int64_t)g->kh * g->kw * x->c * (bits == 1 ? 1 : 6) > ((int64_t)1 << 24))
+        return false;
+    StreamArgs a;
+    memset(&a, 0, sizeof(a));
+    int64_t n = x->n, h = x->h, w = x->w, pb = pixel_bytes64(x);
+    int kh = g->kh, kw = g->kw;
+    a.wrow = (int32_t)(pb * kh * kw);
+    if (!pool && kh == h && kw == w && g->pad_h == 0 && g->pad_w == 0) {
+        pb *= h * w;
+        h = w = kh = kw = 1;
+        ho = wo = 1;
+    }
+    const bool flat = kh == 1 && kw == 1 && !pool && g->pad_h == 0 && g->pad_w == 0 &&
+                      (h * w == 1 || (g->stride_h == 1 && g->stride_w == 1));
+    if (flat) {
+        n *= h * w;
+        h = w = 1;
+        ho = wo = 1;
+    }
+    const int64_t taps = (int64_t)kh * kw;
+    if (taps > 64 || pb > INT32_MAX / 2 || pb % 4 != 0)
+        return false;
+    const int gr = pool ? 2 : 1;
+    a.n = (int32_t)n; a.h = (int32_t)h; a.w_ = (int32_t)w; a.pb = (int32_t)pb;
+    a.m = m;
+    a.epi = e->kind;
+    a.clip_lo = e->clip_lo;
+    a.clip_hi = e->clip_hi;
+    a.pool = pool ? 1 : 0;
+    a.ph = g->pad_h; a.pw = g->pad_w; a.kw = kw; a.taps = (int32_t)taps;
+    // a filter one tap high / wide stages only the rows / columns it reads
+    a.rsh = kh == 1 ? g->stride_h : 1;
+    a.ssh = kh == 1 ? 1 : g->stride_h;
+    a.rsw = kw == 1 ? g->stride_w : 1;
+    a.ssw = kw == 1 ? 1 : g->stride_w;
+    a.ho = pool ? ho / 2 : ho;
+    a.wo = pool ? wo / 2 : wo;
+    const int64_t npix = n * a.ho * a.wo * (pool ? 4 : 1);
+    const int64_t hv = (int64_t)(a.ho * gr - 1) * a.ssh + kh;
+    const int64_t hwd = (int64_t)(a.wo * gr - 1) * a.ssw + kw;
+    if (npix >= ((int64_t)1 << 31) - 1024 || hv > INT32_MAX / 4 || hwd > 8192)
+        return false;
+    a.npix = (int32_t)npix;
+    a.hv = (int32_t)hv;
+    a.hwd = (int32_t)hwd;
+    a.half = (int32_t)((hwd + 1) / 2);
+    a.nblk = (int32_t)((pb + rb - 1) / rb);
+    const int lb = (int)(pb - (int64_t)(a.nblk - 1) * rb);  // packed bytes of the last block
+    const int chunks = (lb * 4 + rb - 1) / rb;
+    a.lg = a.nblk > 1 || chunks > 2 ? 2 : (chunks == 2 ? 1 : 0);
+    const int tps = 4 >> a.lg;
+    a.nlast = (int32_t)((taps + tps - 1) / tps);
+    {
+        const int lt = (int)taps - (a.nlast - 1) * tps;  // taps of the last step
+        a.last2 = a.lg == 2 ? (chunks > 2 ? 1 : 0) : ((lt << a.lg) > 2 ? 1 : 0);
+    }
+    const int run = rb >> (2 - a.lg), ib = run < 16 ? run : 16;
+    a.tail = lb != run ? 1 : 0;
+    a.dw = lb % ib != 0 ? 1 : 0;
+    a.pw1 = taps == 1 && a.lg == 2 ? 1 : 0;
+    const int ps = a.lg == 2 ? 80 : (a.lg == 1 ? 48 : 16);
+    a.div_wo = make_fastdiv((uint32_t)a.wo);
+    a.div_ho = make_fastdiv((uint32_t)a.ho);
+    a.div_hwd = make_fastdiv((uint32_t)hwd);
+    a.div_hv = make_fastdiv((uint32_t)hv);
+    a.div_kw = make_fastdiv((uint32_t)kw);
+    const int nth = e->kind == QNN_EPI_STAIR ? (1 << bits) - 1 : 1;
+    const int64_t steps = a.lg == 2 ? a.nblk * taps : a.nlast;
+
+    double best_cost = 0;
+    variant = -1;
+    const int nv = (int)(sizeof(kStreamTiles) / sizeof(kStreamTiles[0]));
+    for (int v = 0; v < nv; ++v) {
+        const StreamTile &T = kStreamTiles[v];
+        if ((a.lg < 2 || a.tail) && !T.tail)
+            continue;
+        const int MT = 32 * T.wm * T.wch, PT = 32 * T.wn * (4 / T.wch);
+        const int64_t Q = pool ? PT / 4 : PT;
+        // grid rows a tile touches at most, and image boundaries among them
+        int64_t rows = Q % a.wo == 0 ? Q / a.wo : (a.wo % Q == 0 ? 1 : (Q - 2) / a.wo + 2);
+        if (rows > n * a.ho)
+            rows = n * a.ho;
+        int64_t cross = (rows + a.ho - 2) / a.ho;
+        if (Q % a.wo == 0 && rows % a.ho == 0)
+            cross = rows / a.ho - 1;
+        else if (Q % a.wo == 0 && a.ho % rows == 0)
+            cross = 0;
+        if (cross > n - 1)
+            cross = n - 1;
+        const int64_t srows = (rows * gr - 1) * a.ssh + kh + cross * (kh > a.ssh ? kh - a.ssh : 0);
+        const int64_t nslots = a.pw1 ? PT : srows * hwd;
+        if ((cross + 1) * h * w * pb >= 0x7ff00000 || (int64_t)MT * a.wrow >= 0x7ff00000 ||
+            nslots * ps > kLdsBytes)
+            continue;
+        StreamArgs c = a;
+        c.nslots = (int32_t)nslots;
+        c.nbatch = (int32_t)((nslots * (run / ib) + 1023) / 1024);
+        int64_t off = 0;
+        c.off_epi = 0;
+        off += (int64_t)MT * (nth > 1 ? 64 : 32);
+        c.off_sum = (int32_t)off;
+        off += 4 * MT + 16;
+        c.off_pix = (int32_t)off;
+        off += 4 * (nslots + 1);
+        off = (off + 15) & ~(int64_t)15;
+        c.off_w = (int32_t)off;
+        c.off_out = (int32_t)off;
+        const int64_t out_bytes = e->kind == QNN_EPI_RAW32 ? 0 : (pool ? Q * (MT + 16) : Q * (MT * bits / 8 + 4));
+        const int64_t out_end = off + out_bytes;
+        off += 2 * MT * 80;
+        c.off_x = (int32_t)off;
+        c.xbuf = (int32_t)(nslots * ps);
+        off += (int64_t)(a.pw1 ? 2 : 1) * c.xbuf;
+        if (off < out_end)
+            off = out_end;
+        if (off > kLdsBytes)
+            continue;
+        c.lds_bytes = (int32_t)((off + 15) & ~(int64_t)15);
+        const int64_t mtiles = (m + MT - 1) / MT, ptiles = (npix + PT - 1) / PT;
+        if (mtiles * ptiles >= ((int64_t)1 << 23))
+            continue;
+        c.mtiles = (int32_t)mtiles;
+        c.ptiles = (int32_t)ptiles;
+        c.div_mt = make_fastdiv((uint32_t)mtiles);
+        // clocks of the whole grid: a step of one workgroup takes the longest
+        // of its MFMAs, its LDS traffic (128 B per clock) and its loads (about
+        // 32 B per clock and compute unit); a lone workgroup also waits out
+        // the loads' latency, which others on its compute unit cover
+        const int regs_wg = T.wm * T.wn >= 6 ? 2 : (T.wm * T.wn >= 4 ? 3 : 4);
+        int64_t occ = kLdsBytes / c.lds_bytes;
+        if (occ > regs_wg)
+            occ = regs_wg;
+        const int64_t units = mtiles * ptiles;
+        const int64_t conc = (units + kPlanCus - 1) / kPlanCus < occ ? (units + kPlanCus - 1) / kPlanCus : occ;
+        const double xshare = (double)a.nblk / (double)steps;  // blocks per step
+        const double mfma = T.wm * T.wn * 64.0;
+        const double lds = 64.0 * (T.wm + T.wn) + MT * 0.5 + nslots * 0.5 * xshare;
+        const double glob = (MT * (double)rb + nslots * (double)rb * xshare) / 32.0;
+        double thr = mfma > lds ? mfma : lds;
+        if (glob > thr)
+            thr = glob;
+        const double lat = mfma + 700.0;
+        const double per = thr * conc > lat ? thr * conc : lat;
+        const double cost = (double)((units + kPlanCus * conc - 1) / (kPlanCus * conc)) *
+                            (steps * per + 3000.0 + conc * (PT * MT * 0.06 + nslots * rb / 32.0));
+        if (variant < 0 || cost < best_cost) {
+            best = c;
+            best_cost = cost;
+            variant = v;
+        }
+    }
+    return variant >= 0;
+}
+
+// Launches the streaming kernel on a planned layer.
+qnn_status run_stream(StreamArgs &a, int variant, int bits, const void *x_dev, const void *w_dev, const qnn_epi *e,
+                      void *y_dev, int ypb, hipStream_t s)
+{
+    a.x = (const uint8_t *)x_dev;
+    a.w = (const uint8_t *)w_dev;
+    a.y = (uint8_t *)y_dev;
+    a.bias = e->bias;
+    a.mult = e->mult;
+    a.shift = e->shift;
+    a.thresh = e->thresh;
+    a.ypb = ypb;
+    hipError_t (*const launch[4][2])(const StreamArgs &, int, hipStream_t) = {
+        {launch_conv_stream_b1, launch_conv_stream_b1x},
+        {launch_conv_stream_b2, launch_conv_stream_b2x},
+        {launch_conv_stream_b4, launch_conv_stream_b4x},
+        {launch_conv_stream_b8, launch_conv_stream_b8x}};
+    const int lb = bits == 8 ? 3 : (bits == 4 ? 2 : bits - 1);
+    const hipError_t err = launch[lb][a.lg < 2 || a.tail ? 1 : 0](a, variant, s);
+    return err == hipSuccess ? QNN_OK : QNN_ERR_LAUNCH;
+}
+
 qnn_status run_conv(const qnn_tensor *x, const void *x_dev, int32_t m, const void *w_dev,
                     const qnn_conv_geom *g, const qnn_epi *e, const qnn_tensor *y, void *y_dev,
                     void *stream, bool pool = false, const qnn_tile *force = nullptr)
@@ -612,6 +810,10 @@ qnn_status run_conv(const qnn_tensor *x, const void *x_dev, int32_t m, const voi
         st = device_info(&cus);
         if (st != QNN_OK)
             return st;
+        StreamArgs sa;
+        int variant;
+        if (plan_stream(sa, variant, x, m, g, e, ho, wo, pool))
+            return run_stream(sa, variant, 1, x_dev, w_dev, e, y_dev, ypb, s);
         XnorArgs a;
         memset(&a, 0, sizeof(a));
         a.x = (const uint32_t *)x_dev;
@@ -677,12 +879,23 @@ qnn_status run_conv(const qnn_tensor *x, const void *x_dev, int32_t m, const voi
         return QNN_ERR_ALIGN;
 
     // a filter covering the whole image with raw outputs (the network's
-    // classifier): the fully connected kernel, unless the caller forces a tile
+    // classifier): the fully connected kernel, unless the caller forces a
+    // tile.  Its 16x16 tiles read 32 rows of K each, about 10 MB/us in all
+    // from the L2s, while the streaming kernel's time goes with its steps
+    // along K (about 2 us and 0.25 us per 64 staged bytes): 1000 images of
+    // 4096 INT-8 codes to 1000 outputs, 520 MB, 59 against 22 us; 500 images
+    // of 2176 to 93, 13 MB, 4.8 against 12.3 us
     if (!force && e->kind == QNN_EPI_RAW32 && x->bits != 1 && g->kh == x->h && g->kw == x->w &&
         g->pad_h == 0 && g->pad_w == 0 && K % 64 == 0) {
         st = device_info(&cus);
         if (st != QNN_OK)
             return st;
+        const int64_t kb = K * x->bits / 8;
+        const int64_t tiles = (((int64_t)x->n + 15) / 16) * (((int64_t)m + 15) / 16);
+        StreamArgs sa;
+        int variant;
+        if (tiles * 32 * kb > 20000000 + 40000 * kb && plan_stream(sa, variant, x, m, g, e, ho, wo, false))
+            return run_stream(sa, variant, x->bits, x_dev, w_dev, e, y_dev, ypb, s);
         return launch_linear_raw((const uint8_t *)x_dev, (const uint8_t *)w_dev, e->bias, (int32_t *)y_dev,
                                  x->n, m, (int32_t)K, x->bits, s) == hipSuccess ? QNN_OK : QNN_ERR_LAUNCH;
     }
@@ -743,6 +956,18 @@ qnn_status run_conv(const qnn_tensor *x, const void *x_dev, int32_t m, const voi
     st = device_info(&cus);
     if (st != QNN_OK)
         return st;
+    // every layer that the tile kernels take goes to the streaming kernel,
+    // unless the caller forces a tile, except small narrow ones: with at most
+    // 24 output channels and fewer than a quarter of the device's workgroups
+    // the 16-channel tiles of the 16x16 kernel give more of them (7 images of
+    // 59x13x96 INT-4 codes to 23 channels: 7.5 against 10.8 us)
+    if (!force) {
+        StreamArgs sa;
+        int variant;
+        if (plan_stream(sa, variant, x, m, g, e, ho, wo, pool) &&
+            !(!pool && m <= 24 && (int64_t)sa.ptiles * sa.mtiles < cus / 4))
+            return run_stream(sa, variant, x->bits, x_dev, w_dev, e, y_dev, ypb, s);
+    }
     if (use32 && nw == 8 && a.ntiles > cus && !f4) {
         // an eight-wave plan needs one tile per workgroup and one workgroup
         // per compute unit (the e2m1 path also has eight-wave instances that

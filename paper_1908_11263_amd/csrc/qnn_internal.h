@@ -108,6 +108,45 @@ struct ImgArgs {
     const int32_t *thresh; // staircase thresholds [M][2^bits - 1] (EPI_STAIR)
 };
 
+// Arguments of the streaming implicit-GEMM convolution (conv_stream_kernel).
+struct StreamArgs {
+    const uint8_t *x;      // packed NHWC input
+    const uint8_t *w;      // packed OHWI weights
+    uint8_t *y;            // packed NHWC codes (pooled or not) or int32 [pix][M]
+    const int32_t *bias, *mult;
+    const int8_t *shift;
+    const int32_t *thresh;
+    int32_t n, h, w_, pb;  // input size, packed bytes per pixel
+    int32_t m, wrow;       // output channels, packed bytes per filter bank
+    int32_t epi, clip_lo, clip_hi, ypb;
+    int32_t pool, pw1;     // pooled outputs; one-tap filters on the two-operand stream
+    int32_t ph, pw, kw, taps;
+    // staged row r / column c of an image is its input row r*rsh - ph /
+    // column c*rsw - pw; an output step is ssh staged rows / ssw columns
+    int32_t rsh, rsw, ssh, ssw;
+    int32_t ho, wo;        // output rows and columns per image (pooled: windows)
+    int32_t npix;          // outputs in all (pooled: four per window)
+    int32_t hv, hwd, half; // staged rows per image, columns per row, even columns first (ssw = 2)
+    int32_t nslots;        // pixel slots of an input tile
+    int32_t nblk, lg;      // channel blocks of 64 staged bytes; log2 of a tap's 16-byte chunks in a step
+    int32_t nlast;         // steps of a block (lg < 2)
+    int32_t last2;         // the last block's (lg < 2: last step's) second half holds data
+    int32_t nbatch;        // input batches of a block
+    int32_t tail, dw;      // the last block is not full; it ends inside an item (loaded by words)
+    int32_t ptiles, mtiles;
+    int32_t off_epi, off_sum, off_pix, off_w, off_x, off_out, xbuf, lds_bytes;
+    FastDiv div_wo, div_ho, div_hwd, div_hv, div_mt, div_kw;
+};
+
+// Wave tiles of conv_stream_kernel: index, 32-channel and 32-output matrix
+// tiles per wave, waves along the channels (of four).
+#define QNN_STREAM_VARIANTS(X) \
+    X(0, 2, 4, 2) X(1, 2, 3, 2) X(2, 2, 2, 2) X(3, 2, 2, 1) \
+    X(4, 2, 1, 1) X(5, 1, 2, 1) X(6, 1, 1, 1) X(7, 1, 1, 2)
+// ... and of its instances for narrow or odd pixels (LG < 2, TAIL)
+#define QNN_STREAM_VARIANTS_TAIL(X) \
+    X(0, 2, 4, 2) X(2, 2, 2, 2) X(3, 2, 2, 1) X(5, 1, 2, 1) X(6, 1, 1, 1)
+
 // Arguments of the INT-1 XNOR/popcount convolution.
 struct XnorArgs {
     const uint32_t *x;     // packed NHWC bits, cd dwords per pixel
@@ -141,6 +180,15 @@ hipError_t launch_conv_m32_b2(const ConvArgs &a, int wm, int wn, int al16, int n
 // INT-2 and INT-1 through the e2m1 (FP4) matrix instruction
 hipError_t launch_conv_m32_f4(const ConvArgs &a, int wm, int wn, int al16, int nw, dim3 grid, hipStream_t s);
 hipError_t launch_conv_m32_f4b1(const ConvArgs &a, int wm, int wn, int al16, int nw, dim3 grid, hipStream_t s);
+// streaming implicit GEMM: int8 matrix path at 8 and 4 bits, e2m1 at 2 and 1
+hipError_t launch_conv_stream_b8(const StreamArgs &a, int variant, hipStream_t s);
+hipError_t launch_conv_stream_b8x(const StreamArgs &a, int variant, hipStream_t s);
+hipError_t launch_conv_stream_b4(const StreamArgs &a, int variant, hipStream_t s);
+hipError_t launch_conv_stream_b4x(const StreamArgs &a, int variant, hipStream_t s);
+hipError_t launch_conv_stream_b2(const StreamArgs &a, int variant, hipStream_t s);
+hipError_t launch_conv_stream_b2x(const StreamArgs &a, int variant, hipStream_t s);
+hipError_t launch_conv_stream_b1(const StreamArgs &a, int variant, hipStream_t s);
+hipError_t launch_conv_stream_b1x(const StreamArgs &a, int variant, hipStream_t s);
 hipError_t launch_conv_xnor(const XnorArgs &a, hipStream_t s);
 // whole-image kernel; hipErrorInvalidValue for a shape with no built
 // instance; the grid fills the cus compute units with resident workgroups
