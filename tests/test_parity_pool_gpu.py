@@ -108,3 +108,34 @@ def test_pool_cifar_layers_batch4096(qnn, orc, bits):
                             cv["mult"], cv["shift"], None, net.clip, cv["c_alg"])
         check(qnn, orc, L)
         hw //= 2
+
+
+@pytest.mark.parametrize("bits", [8, 4, 2])
+def test_maxpool_lane_widths_and_windows(qnn, orc, bits):
+    """Separate pooling: pixels of whole 16-byte quads and not, windows with
+    and without an instance of their own, extreme codes."""
+    import torch
+    rng = np.random.default_rng(bits)
+    for i, pb in enumerate([4, 12, 16, 20, 32, 48]):
+        c = pb * 8 // bits
+        x = rng.integers(0, 256, size=(3, 9, 11, pb), dtype=np.uint8)
+        x[1] = np.where(rng.integers(0, 2, size=x[1].shape), 255, 0)
+        for (kh, kw, sh, sw) in [(2, 2, 2, 2), (3, 3, 2, 2), (3, 3, 1, 1), (2, 3, 1, 2), (5, 5, 3, 3), (1, 1, 2, 2)]:
+            log("case maxpool bits=%d pb=%d window %dx%d stride %dx%d" % (bits, pb, kh, kw, sh, sw))
+            got = qnn.maxpool2d(dev(x), (3, 9, 11, c), bits, kh, kw, sh, sw)
+            torch.cuda.synchronize()
+            compare(got.cpu().numpy(), orc.maxpool2d(x, (3, 9, 11, c), bits, kh, kw, sh, sw),
+                    "maxpool %d-bit pb=%d" % (bits, pb))
+
+
+@pytest.mark.parametrize("count", [1, 15, 16, 17, 4095, 4096, 4097, 1 << 20])
+def test_relu_remainders(qnn, count):
+    import torch
+    x = np.random.default_rng(count).integers(0, 256, size=count, dtype=np.uint8)
+    d = dev(x)
+    y = qnn.relu_s8(d)
+    qnn.relu_s8(d, out=d)
+    torch.cuda.synchronize()
+    want = np.where(x >= 128, 0, x).astype(np.uint8)
+    compare(y.cpu().numpy(), want, "relu %d" % count)
+    compare(d.cpu().numpy(), want, "relu in place %d" % count)
