@@ -6,10 +6,10 @@
 // leaves the matrix cores waiting for one long staging phase per tile.  Here
 // the reduction runs in steps of 64 staged bytes per channel and pixel:
 //   for each 64-byte block of a pixel's channels, for each filter tap:
-//     one 64-byte slice of the channel tile's filters (two LDS buffers, two
-//     slices in flight) times the block of the input tile, read at the tap's
-//     offset
-// so LDS holds two filter slices and one block of the input tile with its
+//     one 64-byte slice of the channel tile's filters (two LDS buffers of one
+//     or two slices, the next loads in flight) times the block of the input
+//     tile, read at the tap's offset
+// so LDS holds a few filter slices and one block of the input tile with its
 // halo, whatever K is, and each packed byte is unpacked once per tile.
 //
 // Tiles.  A workgroup (4 waves) owns 32*WM*WCH output channels and
@@ -30,16 +30,17 @@
 // result is the integer one bit for bit) at half the staged bytes and twice
 // the rate of int8: 128 channels per 64-byte block.
 //
-// Measured on the device, start of pass to start of pass, against the tile
-// kernels (and XNOR / popcount at 1 bit): 256 images of 14x14x256 INT-8 codes,
-// 256 3x3 filters, 151 -> 38.6 us (1.5 POP/s); INT-1 8x8x256, 256 3x3 filters,
-// batch 1024, 87 -> 20.3 us; 1x1 INT-8 28x28x128 -> 256, batch 256, 65.8 ->
-// 33.7 us; 1000x4096 by 4096x1000 INT-8 58 -> 20.7 us.  What bounds it: where K is
-// long, the main loop (one step is 512 clocks of MFMAs per wave of a 2x4 tile
-// and about as much again of fragment reads, slice stores and the barrier,
-// half covered by the second workgroup of the compute unit); where K is short,
-// the chain of a tile's prologue (parameters, pixel offsets, loads, staging)
-// and its compression, about 10,000 and 8,000 clocks.
+// Measured on the device, passes one after another, against the tile kernels
+// (and XNOR / popcount at 1 bit): 256 images of 14x14x256 INT-8 codes, 256 3x3
+// filters, 151 -> 38.7 us (1.5 POP/s); INT-1 8x8x256, 256 3x3 filters, batch
+// 1024, 87 -> 20.0 us; 1x1 INT-8 28x28x128 -> 256, batch 256, 65.8 -> 30.7 us;
+// INT-4 56x56x64 -> 128, stride 2, staircase, batch 256, 84.6 -> 65.4 us;
+// 1000x4096 by 4096x1000 INT-8 58 -> 19.7 us.  What bounds it: where K is long,
+// the main loop (a 2x4 wave tile's step of 64 K bytes is 512 clocks of MFMAs;
+// with the fragment reads, slice stores and the barrier the loop runs at
+// 60-70% of the matrix rate with two workgroups per compute unit); where K is
+// short, the chain of a tile's prologue (parameters, pixel offsets, loads,
+// staging) and its compression.
 #pragma once
 
 #include "conv_m32_impl.h"
@@ -150,10 +151,13 @@ enum { STREAM_CODES = 0, STREAM_RAW = 1, STREAM_POOL = 2 };
 // Otherwise the input block stays for all taps in one LDS buffer; the next
 // block's loads are issued in its first two steps, held in registers and
 // stored after its last (batches past the second are loaded there).
-template <int BITS, int WM, int WN, int WCH, int MODE, int LG, bool TAIL, bool PW>
+// G: filter slices per step (between two barriers).  Two save 3-8% unless their
+// LDS costs a workgroup of a compute unit.
+template <int BITS, int WM, int WN, int WCH, int G, int MODE, int LG, bool TAIL, bool PW>
 __global__ void __launch_bounds__(256, (WM * WN >= 6 ? 2 : (WM * WN >= 4 ? 3 : 4))) conv_stream_kernel(StreamArgs a)
 {
     extern __shared__ __align__(16) uint8_t smem[];
+    static_assert(!PW || G == 1, "one-tap filters bring new input with every slice");
     constexpr bool F4 = BITS <= 2;
     constexpr int WPX = 4 / WCH;
     constexpr int MT = 32 * WM * WCH;
@@ -163,13 +167,13 @@ __global__ void __launch_bounds__(256, (WM * WN >= 6 ? 2 : (WM * WN >= 4 ? 3 : 4
     constexpr int LB = RUN < 16 ? RUN : 16;         // packed bytes of an item
     constexpr int QPR = RUN / LB, TPS = 4 >> LG;    // items per run, taps per step
     constexpr int IPR = TPS * QPR;                  // filter items per row and step
-    constexpr int WS = 80;                          // LDS strides: odd multiples of 16 bytes
+    constexpr int D = 3 - G;                         // filter loads are issued D steps ahead
+    constexpr int WS = 64 * G + 16;                 // LDS strides: odd multiples of 16 bytes
     constexpr int PS = LG == 2 ? 80 : (LG == 1 ? 48 : 16);
     constexpr int SPX = (16 << LG) / QPR;           // staged bytes of an input item
     constexpr int UW = (MT * IPR + 255) / 256;      // filter items per thread and step
-    constexpr int UX = 4;                           // input items per thread and batch
-    // filter slices in flight: their loads take longer than a step
-    constexpr int D = 2;
+    // input items per thread and batch
+    constexpr int UX = PW ? (PT * QPR + 255) / 256 : 4;
     // log2 of the weight scale the accumulator carries (4-bit filters are staged as 16 w)
     constexpr int SL = BITS == 4 ? 4 : 0;
     constexpr int NTH = BITS == 8 ? 1 : (1 << BITS) - 1;
@@ -207,16 +211,14 @@ __global__ void __launch_bounds__(256, (WM * WN >= 6 ? 2 : (WM * WN >= 4 ? 3 : 4
     const __amdgpu_buffer_rsrc_t wr = stream_rsrc(a.w + (size_t)m0 * (uint32_t)a.wrow, (uint32_t)(mrows * a.wrow));
     const int nblk = LG == 2 ? a.nblk : 1;
     const int lastb = nblk - 1;
-    const int spb = LG == 2 ? a.taps : a.nlast;        // steps per block
-    // ... rounded up to whole groups of D steps, so that each step's register
-    // set is fixed and no load is conditional (a load that may or may not be
-    // in flight turns the waits around it into waits for everything); the
-    // steps added load and multiply nothing
-    const int spp = PW ? 1 : (spb + D - 1) / D * D;
+    const int spb = LG == 2 ? a.taps : a.nlast;        // slices per block
+    // steps per block: with two register sets an even number, so that each
+    // step's set is fixed (the step added loads and multiplies nothing)
+    const int ns = PW ? 1 : (spb + 1) / 2 * D;
     const int pb = a.pb, taps = a.taps;
 
     // filter slice of a step: item u of this thread
-    uint4 wq[D][UW];
+    uint4 wq[D][G * UW];
     uint32_t wvo[UW];
     int wsum[UW];
     const int qn = (uint32_t)tid % QPR;                           // the item's place in its run (256 % IPR = 0)
@@ -229,8 +231,9 @@ __global__ void __launch_bounds__(256, (WM * WN >= 6 ? 2 : (WM * WN >= 4 ? 3 : 4
         wvo[u] = row < mrows ? (uint32_t)(row * a.wrow + wtap * pb + qn * LB) : kStreamOob;
         wsum[u] = 0;
     }
-    // (steps that only fill a group, and those past the last, load slice 0;
-    // it is not stored)
+    // (no load is conditional: one that may or may not be in flight turns the
+    // waits around it into waits for everything.  Slices past a block's or the
+    // last one load slice 0, which is not stored.)
     auto w_load = [&](uint4 *q, int cb, int t) {
         const uint32_t so = cb < nblk && t < spb ? (uint32_t)(t * TPS * pb + cb * RB) : 0u;
         const bool live = (TPS == 1 || t * TPS + wtap < taps) && (!TAIL || cb != lastb || nvw > 0);
@@ -268,11 +271,13 @@ __global__ void __launch_bounds__(256, (WM * WN >= 6 ? 2 : (WM * WN >= 4 ? 3 : 4
             }
         }
     };
-    // the next slice to load
+    // the next step whose slices are loaded
     int lcb = 0, lt = 0;
     auto w_next = [&](uint4 *q) {
-        w_load(q, lcb, lt);
-        if (++lt == spp) {
+#pragma unroll
+        for (int g = 0; g < G; ++g)
+            w_load(q + g * UW, lcb, lt * G + g);
+        if (++lt == ns) {
             lt = 0;
             ++lcb;
         }
@@ -369,9 +374,14 @@ __global__ void __launch_bounds__(256, (WM * WN >= 6 ? 2 : (WM * WN >= 4 ? 3 : 4
         uint8_t *sX = smem + a.off_x + buf * a.xbuf + qn * SPX;
 #pragma unroll
         for (int u = 0; u < UX; ++u) {
-            const int slot = (int)((uint32_t)(b * (256 * UX) + tid + u * 256) / QPR);
+            const int first = b * (256 * UX) + u * 256;
+            if (!PW && first >= nslots * QPR)
+                break;
+            const int slot = (int)((uint32_t)(first + tid) / QPR);
             if (slot < nslots)
                 stream_store<BITS, F4, false, LB>(sX + slot * PS, q[u], 4);
+            if (BITS != 8)
+                __builtin_amdgcn_sched_barrier(0);  // (unpacked together they would spill)
         }
     };
     if (PW) {
@@ -439,13 +449,6 @@ __global__ void __launch_bounds__(256, (WM * WN >= 6 ? 2 : (WM * WN >= 4 ? 3 : 4
         else
             base[c] = (vr * a.hwd + (a.ssw == 2 ? ox : ox * a.ssw)) * PS + a.off_x + (LG > 0 ? h * 16 : 0);
     }
-    typedef typename AccTile<F4>::type ACC;
-    ACC acc[WM][WN];
-#pragma unroll
-    for (int i = 0; i < WM; ++i)
-#pragma unroll
-        for (int c = 0; c < WN; ++c)
-            acc[i][c] = (ACC){};
     const int wlane = (wch * 32 * WM + r32) * WS + h * 16;
 
     // input block 0 and the first filter slice
@@ -459,10 +462,20 @@ __global__ void __launch_bounds__(256, (WM * WN >= 6 ? 2 : (WM * WN >= 4 ? 3 : 4
             x_store(xq[1], b + 1, 0);
         }
     }
-    w_store(wq[0], 0, 0, a.off_w);
+#pragma unroll
+    for (int g = 0; g < G; ++g)
+        if (g == 0 || g < spb)
+            w_store(wq[0] + g * UW, 0, g, a.off_w + 64 * g);
     stream_barrier();
 
     // ---- main loop ----
+    typedef typename AccTile<F4>::type ACC;
+    ACC acc[WM][WN];
+#pragma unroll
+    for (int i = 0; i < WM; ++i)
+#pragma unroll
+        for (int c = 0; c < WN; ++c)
+            acc[i][c] = (ACC){};
     // lane t holds tap t's offset in the input tile (a scalar read per step);
     // taps past the last one meet zero weights and read slot 0
     int tapv = 0;
@@ -490,21 +503,29 @@ __global__ void __launch_bounds__(256, (WM * WN >= 6 ? 2 : (WM * WN >= 4 ? 3 : 4
     };
     int cb = 0, t = 0;
     int rb = a.off_w, wb = a.off_w + MT * WS;  // filter buffers read and written by the step
-    // XL: the batch of the next input block whose loads this step issues (-1: none)
+    // S: the register set of a step's filter loads; XL: issues the loads of
+    // the next input block's first two batches
     auto step = [&](auto slot, auto xl) {
-        constexpr int S = decltype(slot)::value, XL = decltype(xl)::value;
-        const bool block_end = t + 1 == spp;
+        constexpr int S = decltype(slot)::value;
+        constexpr bool XL = decltype(xl)::value != 0;
+        const bool block_end = t + 1 == ns;
         const int ncb = block_end ? cb + 1 : cb, nt = block_end ? 0 : t + 1;
-        // loads of the filter slice D steps ahead, and of the input
         w_next(wq[S]);
-        if (PW)
+        if (PW) {
             x_load(xq[S & 1], cb + 2, 0);
-        else if (XL >= 0)
-            x_load(xq[XL & 1], cb + 1, XL);
-        if (PW || t < spb) {
+        } else if (XL) {
+            x_load(xq[0], cb + 1, 0);
+            x_load(xq[1], cb + 1, 1);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+            const int sl = t * G + g;
+            if (!PW && sl >= spb)
+                break;
             int o0, o1;
-            x_offs(cb, t, o0, o1);
-            const uint8_t *wp = smem + rb + wlane;
+            x_offs(cb, sl, o0, o1);
+            const uint8_t *wp = smem + rb + wlane + 64 * g;
             v4i xf[2][WN], wf[2][WM];
             auto frags = [&](int ks) {
 #pragma unroll
@@ -530,35 +551,51 @@ __global__ void __launch_bounds__(256, (WM * WN >= 6 ? 2 : (WM * WN >= 4 ? 3 : 4
             __builtin_amdgcn_sched_barrier(0);
             mfmas(0);
             // (the second half of the last block may be all padding)
-            if (!TAIL || cb != lastb || a.last2 || (LG < 2 && t + 1 != spb)) {
+            if (!TAIL || cb != lastb || a.last2 || (LG < 2 && sl + 1 != spb)) {
                 frags(1);
                 mfmas(1);
             }
         }
-        // the next slice, unless there is none or the next step only fills a group
-        if (ncb < nblk && (PW || nt < spb))
-            w_store(wq[(S + 1) % D], ncb, nt, wb);
-        if (PW)
-            x_store(xq[(S + 1) & 1], 0, ncb & 1);
+        if (ncb < nblk) {
+#pragma unroll
+            for (int g = 0; g < G; ++g)
+                if (PW || nt * G + g < spb)
+                    w_store(wq[(S + 1) % D] + g * UW, ncb, nt * G + g, wb + 64 * g);
+            if (PW)
+                x_store(xq[(S + 1) & 1], 0, ncb & 1);
+        }
         stream_barrier();
-        const bool done = cb == lastb && t + 1 == spb;
         cb = ncb;
         t = nt;
         const int sw = rb;
         rb = wb;
         wb = sw;
-        return done;
     };
-    using None = StreamInt<-1>;
-    for (;;) {
-        constexpr int X0 = LG == 2 && !PW ? 0 : -1, X1 = LG == 2 && !PW ? 1 : -1;
-        bool done = step(StreamInt<0>(), StreamInt<X0>()) || step(StreamInt<1>(), StreamInt<X1>());
-        if (!PW)
-            while (!done && t != 0)
-                done = step(StreamInt<0>(), None()) || step(StreamInt<1>(), None());
-        if (done)
-            break;
-        if (!PW) {
+    using No = StreamInt<0>;
+    if constexpr (PW) {
+        for (;;) {
+            step(StreamInt<0>(), No());
+            if (cb == nblk)
+                break;
+            step(StreamInt<1>(), No());
+            if (cb == nblk)
+                break;
+        }
+    } else {
+        for (;;) {
+            step(StreamInt<0>(), StreamInt<(LG == 2 ? 1 : 0)>());
+            if constexpr (D == 1) {
+                while (t != 0)
+                    step(StreamInt<0>(), No());
+            } else {
+                step(StreamInt<1>(), No());
+                while (t != 0) {
+                    step(StreamInt<0>(), No());
+                    step(StreamInt<1>(), No());
+                }
+            }
+            if (cb == nblk)
+                break;
             // every wave is done with the block: the next one takes its place
             x_store(xq[0], 0, 0);
             x_store(xq[1], 1, 0);
@@ -617,10 +654,15 @@ __global__ void __launch_bounds__(256, (WM * WN >= 6 ? 2 : (WM * WN >= 4 ? 3 : 4
         return (__umul24(dc, (uint32_t)e[2]) + (uint32_t)e[3]) >> e[4];
     };
     auto code4 = [&](int32_t x, const int32_t *e) {
+        // the 48-bit product of two 24-bit numbers from its full-rate halves
+        // (a 32x32->64 multiply-add and a 64-bit shift take four times as long)
         const int32_t d = __builtin_elementwise_sub_sat(x, e[0]);
         const uint32_t dc = (uint32_t)min(max(d, 0), e[1]);
-        const uint64_t rs = ((uint64_t)(uint32_t)e[5] << 32) | (uint32_t)e[3];
-        return (uint32_t)(((uint64_t)dc * (uint32_t)e[2] + rs) >> e[4]);
+        uint32_t hi;
+        __asm__("v_mul_hi_u32_u24 %0, %1, %2" : "=v"(hi) : "v"(dc), "v"(e[2]));
+        const uint32_t lo = __umul24(dc, (uint32_t)e[2]), sum = lo + (uint32_t)e[3];
+        hi += (uint32_t)e[5] + (sum < lo ? 1u : 0u);
+        return __builtin_amdgcn_alignbit(hi, sum, (uint32_t)e[4]);
     };
     auto code_any = [&](int32_t x, const int32_t *e, int32_t sum) -> uint32_t {
         if (e[6] >= 3)
@@ -659,128 +701,19 @@ __global__ void __launch_bounds__(256, (WM * WN >= 6 ? 2 : (WM * WN >= 4 ? 3 : 4
         constexpr int CS = OB + 4;                   // LDS bytes per output of the indirect path
         constexpr int TB = 4 * BITS;                 // output bytes of 32 channels
         const bool direct = (a.ypb % (BITS == 1 ? 4 : TB / 2)) == 0 && obn == OB;
-#pragma unroll
-        for (int i = 0; i < WM; ++i) {
-            const int chw = wch * 32 * WM + i * 32;
-            uint32_t word[WN][4];
-#pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                const int ch = chw + 8 * g + 4 * h;
-#pragma unroll
-                for (int c = 0; c < WN; ++c)
-                    word[c][g] = 0;
-                if (thr) {
-                    if constexpr (NTH == 1) {
-                        const int4 T = *(const int4 *)(sP + ch);
-#pragma unroll
-                        for (int c = 0; c < WN; ++c)
-                            word[c][g] = ((int32_t)acc[i][c][4 * g] >= T.x ? 1u : 0u) |
-                                         ((int32_t)acc[i][c][4 * g + 1] >= T.y ? 2u : 0u) |
-                                         ((int32_t)acc[i][c][4 * g + 2] >= T.z ? 4u : 0u) |
-                                         ((int32_t)acc[i][c][4 * g + 3] >= T.w ? 8u : 0u);
-                    } else {
-#pragma unroll
-                        for (int k = 0; k < 4; ++k) {
-                            const int32_t *col = sP + (ch + k) * 16;
-                            if (NTH == 15 && (votes & 4)) {
-                                // sorted: the balanced tree, its last two
-                                // levels' thresholds read from LDS
-                                const int32_t t3 = col[3], t7 = col[7], t11 = col[11];
-#pragma unroll
-                                for (int c = 0; c < WN; ++c) {
-                                    const int32_t x = (int32_t)acc[i][c][4 * g + k];
-                                    uint32_t q = x >= t7 ? 1u : 0u;
-                                    q = stair_bit(q, x, q ? t11 : t3);
-                                    q = stair_bit(q, x, col[4 * q + 1]);
-                                    word[c][g] |= stair_bit(q, x, col[2 * q]) << (k * BITS);
-                                }
-                            } else if (NTH == 3) {
-                                const int4 T = *(const int4 *)col;
-#pragma unroll
-                                for (int c = 0; c < WN; ++c) {
-                                    const int32_t x = (int32_t)acc[i][c][4 * g + k];
-                                    word[c][g] |= ((x >= T.x ? 1u : 0u) + (x >= T.y ? 1u : 0u) + (x >= T.z ? 1u : 0u))
-                                                  << (k * BITS);
-                                }
-                            } else {
-#pragma unroll 1
-                                for (int j = 0; j < NTH; ++j) {
-                                    const int32_t tj = col[j];
-#pragma unroll
-                                    for (int c = 0; c < WN; ++c)
-                                        word[c][g] += (int32_t)acc[i][c][4 * g + k] >= tj ? 1u << (k * BITS) : 0u;
-                                }
-                            }
-                        }
-                    }
-                } else if (BITS != 1) {
-                    int32_t e[4][7], sum[4];
-#pragma unroll
-                    for (int f = 0; f < 7; ++f) {
-                        const int4 q = *(const int4 *)(sP + f * MT + ch);
-                        e[0][f] = q.x;
-                        e[1][f] = q.y;
-                        e[2][f] = q.z;
-                        e[3][f] = q.w;
-                    }
-                    if (BITS == 8) {
-                        const int4 q = *(const int4 *)(sSum + ch);
-                        sum[0] = q.x;
-                        sum[1] = q.y;
-                        sum[2] = q.z;
-                        sum[3] = q.w;
-                    }
-#pragma unroll
-                    for (int k = 0; k < 4; ++k)
-                        fold(e[k], BITS == 8 ? sum[k] : 0);
-                    if (votes & 1) {
-#pragma unroll
-                        for (int c = 0; c < WN; ++c)
-#pragma unroll
-                            for (int k = 0; k < 4; ++k)
-                                word[c][g] |= code3((int32_t)acc[i][c][4 * g + k], e[k]) << (k * BITS);
-                    } else if (votes & 2) {
-#pragma unroll
-                        for (int c = 0; c < WN; ++c)
-#pragma unroll
-                            for (int k = 0; k < 4; ++k)
-                                word[c][g] |= code4((int32_t)acc[i][c][4 * g + k], e[k]) << (k * BITS);
-                    } else {
-                        // rare: one channel at a time, the registers rotated
-                        // through the first
-                        int32_t x[WN][4];
-#pragma unroll
-                        for (int c = 0; c < WN; ++c)
-#pragma unroll
-                            for (int k = 0; k < 4; ++k)
-                                x[c][k] = (int32_t)acc[i][c][4 * g + k];
-#pragma unroll 1
-                        for (int k = 0; k < 4; ++k) {
-#pragma unroll
-                            for (int c = 0; c < WN; ++c) {
-                                word[c][g] |= code_any(x[c][0], e[0], BITS == 8 ? sum[0] : 0) << (k * BITS);
-                                x[c][0] = x[c][1];
-                                x[c][1] = x[c][2];
-                                x[c][2] = x[c][3];
-                            }
-#pragma unroll
-                            for (int j = 0; j < 3; ++j) {
-#pragma unroll
-                                for (int f = 0; f < 7; ++f)
-                                    e[j][f] = e[j + 1][f];
-                                sum[j] = sum[j + 1];
-                            }
-                        }
-                    }
-                }
-            }
+        // stores of matrix tile row i (addresses from an opaque copy of p0: they
+        // would otherwise be kept in registers through the main loop)
+        int pe = p0;
+        __asm__ volatile("" : "+s"(pe));
+        uint8_t *const yl = a.y + (size_t)(pe + wpx * 32 * WN + r32) * (uint32_t)a.ypb + ob0 + wch * WM * TB;
+        auto emit = [&](int i, uint32_t (*word)[4]) {
 #pragma unroll
             for (int c = 0; c < WN; ++c) {
                 const int pl = wpx * 32 * WN + c * 32 + r32;
+                const bool ok = pe + pl < a.npix;
                 uint32_t *w = word[c];
-                uint8_t *d = direct ? a.y + (size_t)(p0 + pl) * (uint32_t)a.ypb + ob0 + chw * BITS / 8
-                                    : sC + pl * CS + chw * BITS / 8;
-                const bool ok = !direct || p0 + pl < a.npix;
+                uint8_t *d = yl + (size_t)(c * 32) * (uint32_t)a.ypb + i * TB;
+                uint32_t *l = (uint32_t *)(sC + pl * CS + (wch * WM + i) * TB);
                 if constexpr (BITS == 8) {
                     // the halves trade groups: 16 consecutive channels each
                     const auto s0 = __builtin_amdgcn_permlane32_swap(w[0], w[2], false, false);
@@ -789,11 +722,11 @@ __global__ void __launch_bounds__(256, (WM * WN >= 6 ? 2 : (WM * WN >= 4 ? 3 : 4
                         if (ok)
                             *(uint4 *)(d + 16 * h) = make_uint4(s0[0], s0[1], s1[0], s1[1]);
                     } else {
-                        uint32_t *d4 = (uint32_t *)(d + 16 * h);
-                        d4[0] = s0[0];
-                        d4[1] = s0[1];
-                        d4[2] = s1[0];
-                        d4[3] = s1[1];
+                        l[4 * h] = s0[0];
+                        l[4 * h + 1] = s0[1];
+                        l[4 * h + 2] = s1[0];
+                        l[4 * h + 3] = s1[1];
+                        __asm__ volatile("" ::: "memory");  // keeps the two paths' stores apart
                     }
                 } else if constexpr (BITS == 4) {
                     const auto s0 = __builtin_amdgcn_permlane32_swap(w[0] | (w[1] << 16), w[2] | (w[3] << 16), false, false);
@@ -803,26 +736,219 @@ __global__ void __launch_bounds__(256, (WM * WN >= 6 ? 2 : (WM * WN >= 4 ? 3 : 4
                         if (ok)
                             *(uint2 *)(d + 8 * h) = make_uint2(u0, u1);
                     } else {
-                        uint32_t *d4 = (uint32_t *)(d + 8 * h);
-                        d4[0] = u0;
-                        d4[1] = u1;
+                        l[2 * h] = u0;
+                        l[2 * h + 1] = u1;
+                        __asm__ volatile("" ::: "memory");
                     }
                 } else if constexpr (BITS == 2) {
-                    // bytes (group, half) -> group-major
+                    // bytes (group, half) -> group-major; after the swap of a
+                    // register with itself both halves hold the lower half's
+                    // bytes in one and the upper half's in the other
                     const uint32_t r = w[0] | (w[1] << 8) | (w[2] << 16) | (w[3] << 24);
                     const auto s0 = __builtin_amdgcn_permlane32_swap(r, r, false, false);
-                    // both halves now hold the lower half's bytes in one
-                    // register and the upper half's in the other
                     const uint32_t u = __builtin_amdgcn_perm(s0[1], s0[0], h ? 0x07030602u : 0x05010400u);
-                    if (ok)
+                    if (!direct) {
+                        l[h] = u;
+                        __asm__ volatile("" ::: "memory");
+                    } else if (ok) {
                         *(uint32_t *)(d + 4 * h) = u;
+                    }
                 } else {
                     const uint32_t r = w[0] | (w[1] << 8) | (w[2] << 16) | (w[3] << 24);
                     const auto s0 = __builtin_amdgcn_permlane32_swap(r, r, false, false);
-                    if (ok && h == 0)
+                    if (!direct) {
+                        l[0] = s0[0] | (s0[1] << 4);
+                        __asm__ volatile("" ::: "memory");
+                    } else if (ok && h == 0) {
                         *(uint32_t *)d = s0[0] | (s0[1] << 4);
+                    }
                 }
             }
+        };
+        // plan words f of channels ch .. ch + 3
+        auto plan4 = [&](int f, int ch, int32_t *e) {
+            const int4 q = *(const int4 *)(sP + f * MT + ch);
+            e[0] = q.x;
+            e[1] = q.y;
+            e[2] = q.z;
+            e[3] = q.w;
+        };
+        // One form of the compression over the wave's tiles: each form is one
+        // run of code without the others' in between (a workgroup often runs
+        // it once: what it costs is fetching it).  FORM 0: one threshold, 1:
+        // sorted staircase, 2: any staircase, 3 / 4: 32- / 64-bit plans, 5:
+        // any plan.
+        auto run = [&](auto form) {
+            constexpr int FORM = decltype(form)::value;
+            __asm__ volatile("" ::"n"(FORM) : "memory");  // nothing of it moves above the choice
+#pragma unroll
+            for (int i = 0; i < WM; ++i) {
+                uint32_t word[WN][4];
+#pragma unroll
+                for (int g = 0; g < 4; ++g) {
+                    const int ch = wch * 32 * WM + i * 32 + 8 * g + 4 * h;
+                    int32_t x[WN][4];
+#pragma unroll
+                    for (int c = 0; c < WN; ++c) {
+                        word[c][g] = 0;
+#pragma unroll
+                        for (int k = 0; k < 4; ++k)
+                            x[c][k] = (int32_t)acc[i][c][4 * g + k];
+                    }
+                    if constexpr (FORM == 0) {
+                        int32_t T[4];
+                        plan4(0, ch, T);
+#pragma unroll
+                        for (int c = 0; c < WN; ++c)
+#pragma unroll
+                            for (int k = 0; k < 4; ++k)
+                                word[c][g] |= x[c][k] >= T[k] ? 1u << k : 0u;
+                    } else if constexpr (FORM == 1) {
+                        // balanced tree; the last two levels' thresholds come
+                        // from the channel's row in LDS, the reads of all the
+                        // group's codes of a level in flight together
+                        uint32_t q[WN][4];
+                        int32_t t[WN][4];
+                        constexpr int KS = WM * WN >= 6 ? 2 : 4;  // channels at a time (registers)
+#pragma unroll
+                        for (int k0 = 0; k0 < 4; k0 += KS) {
+#pragma unroll
+                            for (int k = k0; k < k0 + KS; ++k) {
+                                const int32_t *col = sP + (ch + k) * 16;
+                                const int32_t t3 = col[3], t7 = col[7], t11 = col[11];
+#pragma unroll
+                                for (int c = 0; c < WN; ++c) {
+                                    q[c][k] = x[c][k] >= t7 ? 1u : 0u;
+                                    q[c][k] = stair_bit(q[c][k], x[c][k], q[c][k] ? t11 : t3);
+                                }
+                            }
+#pragma unroll
+                            for (int l = 2; l >= 1; --l) {
+#pragma unroll
+                                for (int k = k0; k < k0 + KS; ++k)
+#pragma unroll
+                                    for (int c = 0; c < WN; ++c)
+                                        t[c][k] = sP[(ch + k) * 16 + 2 * l * q[c][k] + (l - 1)];
+#pragma unroll
+                                for (int k = k0; k < k0 + KS; ++k)
+#pragma unroll
+                                    for (int c = 0; c < WN; ++c)
+                                        q[c][k] = stair_bit(q[c][k], x[c][k], t[c][k]);
+                            }
+                            __builtin_amdgcn_sched_barrier(0);
+                        }
+#pragma unroll
+                        for (int c = 0; c < WN; ++c)
+                            word[c][g] = q[c][0] | (q[c][1] << BITS) | (q[c][2] << (2 * BITS)) | (q[c][3] << (3 * BITS));
+                    } else if constexpr (FORM == 2) {
+#pragma unroll
+                        for (int k = 0; k < 4; ++k) {
+                            const int32_t *col = sP + (ch + k) * 16;
+                            if constexpr (NTH == 3) {
+                                const int4 T = *(const int4 *)col;
+#pragma unroll
+                                for (int c = 0; c < WN; ++c)
+                                    word[c][g] |= ((x[c][k] >= T.x ? 1u : 0u) + (x[c][k] >= T.y ? 1u : 0u) +
+                                                   (x[c][k] >= T.z ? 1u : 0u)) << (k * BITS);
+                            } else {
+#pragma unroll 1
+                                for (int j = 0; j < NTH; ++j) {
+                                    const int32_t tj = col[j];
+#pragma unroll
+                                    for (int c = 0; c < WN; ++c)
+                                        word[c][g] += x[c][k] >= tj ? 1u << (k * BITS) : 0u;
+                                }
+                            }
+                        }
+                    } else {
+                        int32_t e[7][4], sum[4] = {0, 0, 0, 0};
+#pragma unroll
+                        for (int f = 0; f < (FORM == 3 ? 5 : (FORM == 4 ? 6 : 7)); ++f)
+                            plan4(f, ch, e[f]);
+                        if (BITS == 8) {
+                            const int4 q = *(const int4 *)(sSum + ch);
+                            sum[0] = q.x;
+                            sum[1] = q.y;
+                            sum[2] = q.z;
+                            sum[3] = q.w;
+#pragma unroll
+                            for (int k = 0; k < 4; ++k)
+                                if (FORM != 5 || e[6][k] != 0)
+                                    e[0][k] = __builtin_elementwise_sub_sat(e[0][k], sum[k]);
+                        }
+                        if constexpr (FORM < 5) {
+#pragma unroll
+                            for (int c = 0; c < WN; ++c)
+#pragma unroll
+                                for (int k = 0; k < 4; ++k) {
+                                    const int32_t ek[7] = {e[0][k], e[1][k], e[2][k], e[3][k], e[4][k], FORM == 4 ? e[5][k] : 0, 3};
+                                    word[c][g] |= (FORM == 3 ? code3(x[c][k], ek) : code4(x[c][k], ek)) << (k * BITS);
+                                }
+                        } else {
+                            // one code at a time, everything rotated through
+                            // the first registers (rare: small code)
+                            int32_t z[4 * WN];
+                            uint32_t w[WN];
+#pragma unroll
+                            for (int c = 0; c < WN; ++c) {
+                                w[c] = 0;
+#pragma unroll
+                                for (int k = 0; k < 4; ++k)
+                                    z[k * WN + c] = x[c][k];
+                            }
+                            int c = 0, sh = 0;
+#pragma unroll 1
+                            for (int t = 0; t < 4 * WN; ++t) {
+                                const int32_t ek[7] = {e[0][0], e[1][0], e[2][0], e[3][0], e[4][0], e[5][0], e[6][0]};
+                                const uint32_t wn = w[0] | (code_any(z[0], ek, sum[0]) << sh);
+#pragma unroll
+                                for (int v = 0; v + 1 < 4 * WN; ++v)
+                                    z[v] = z[v + 1];
+#pragma unroll
+                                for (int v = 0; v + 1 < WN; ++v)
+                                    w[v] = w[v + 1];
+                                w[WN - 1] = wn;
+                                if (++c == WN) {
+                                    c = 0;
+                                    sh += BITS;
+#pragma unroll
+                                    for (int v = 0; v < 3; ++v) {
+#pragma unroll
+                                        for (int f = 0; f < 7; ++f)
+                                            e[f][v] = e[f][v + 1];
+                                        sum[v] = sum[v + 1];
+                                    }
+                                }
+                            }
+#pragma unroll
+                            for (int v = 0; v < WN; ++v)
+                                word[v][g] = w[v];
+                        }
+                    }
+                    // computed here (the compiler would sink it into the
+                    // stores' branches and keep its inputs in scratch memory)
+#pragma unroll
+                    for (int c = 0; c < WN; ++c)
+                        __asm__ volatile("" : "+v"(word[c][g]));
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                emit(i, word);
+            }
+        };
+        if (BITS == 1 || (BITS != 8 && thr)) {
+            if constexpr (NTH == 1)
+                run(StreamInt<0>());
+            else if (NTH == 15 && (votes & 4))
+                run(StreamInt<1>());
+            else
+                run(StreamInt<2>());
+        } else if constexpr (BITS != 1) {
+            if (votes & 1)
+                run(StreamInt<3>());
+            else if (votes & 2)
+                run(StreamInt<4>());
+            else
+                run(StreamInt<5>());
         }
         if (direct)
             return;
@@ -959,9 +1085,9 @@ hipError_t launch_conv_stream_bits(const StreamArgs &a, int variant, hipStream_t
 {
     const int mode = a.pool ? STREAM_POOL : (a.epi == EPI_RAW32 ? STREAM_RAW : STREAM_CODES);
     const dim3 grid((unsigned)(a.ptiles * a.mtiles));
-#define QNN_STREAM_M(V_, WM_, WN_, WCH_, MODE_, LG_, TAIL_, PW_)                                      \
+#define QNN_STREAM_M(V_, WM_, WN_, WCH_, G_, MODE_, LG_, TAIL_, PW_)                                  \
     if (variant == V_ && mode == MODE_ && a.lg == LG_ && a.pw1 == PW_) {                              \
-        auto *k = conv_stream_kernel<BITS, WM_, WN_, WCH_, MODE_, LG_, TAIL_, PW_>;                        \
+        auto *k = conv_stream_kernel<BITS, WM_, WN_, WCH_, G_, MODE_, LG_, TAIL_, PW_>;               \
         if (a.lds_bytes > 64 * 1024 &&                                                                \
             hipFuncSetAttribute((const void *)k, hipFuncAttributeMaxDynamicSharedMemorySize,          \
                                 160 * 1024) != hipSuccess)                                            \
@@ -969,20 +1095,25 @@ hipError_t launch_conv_stream_bits(const StreamArgs &a, int variant, hipStream_t
         hipLaunchKernelGGL(k, grid, dim3(256), a.lds_bytes, s, a);                                    \
         return hipGetLastError();                                                                     \
     }
-#define QNN_STREAM_L(V_, WM_, WN_, WCH_, LG_, TAIL_, PW_)                                              \
-    QNN_STREAM_M(V_, WM_, WN_, WCH_, STREAM_CODES, LG_, TAIL_, PW_)                                        \
-    QNN_STREAM_M(V_, WM_, WN_, WCH_, STREAM_RAW, LG_, TAIL_, PW_)                                          \
+#define QNN_STREAM_L(V_, WM_, WN_, WCH_, G_, LG_, TAIL_, PW_)                                         \
+    QNN_STREAM_M(V_, WM_, WN_, WCH_, G_, STREAM_CODES, LG_, TAIL_, PW_)                               \
+    QNN_STREAM_M(V_, WM_, WN_, WCH_, G_, STREAM_RAW, LG_, TAIL_, PW_)                                 \
     if constexpr (BITS != 1) {                                                                        \
-        QNN_STREAM_M(V_, WM_, WN_, WCH_, STREAM_POOL, LG_, TAIL_, PW_)                                     \
+        QNN_STREAM_M(V_, WM_, WN_, WCH_, G_, STREAM_POOL, LG_, TAIL_, PW_)                            \
     }
-#define QNN_STREAM_0(V_, WM_, WN_, WCH_)                                                              \
-    QNN_STREAM_L(V_, WM_, WN_, WCH_, 2, false, false)                                                 \
-    QNN_STREAM_L(V_, WM_, WN_, WCH_, 2, false, true)
-#define QNN_STREAM_1(V_, WM_, WN_, WCH_)                                                              \
-    QNN_STREAM_L(V_, WM_, WN_, WCH_, 2, true, false)                                                  \
-    QNN_STREAM_L(V_, WM_, WN_, WCH_, 2, true, true)                                                   \
-    QNN_STREAM_L(V_, WM_, WN_, WCH_, 1, true, false)                                                  \
-    QNN_STREAM_L(V_, WM_, WN_, WCH_, 0, true, false)
+    // one-tap filters (of one tap per step): G = 1 only
+#define QNN_STREAM_0(V_, WM_, WN_, WCH_, G_)                                                          \
+    QNN_STREAM_L(V_, WM_, WN_, WCH_, G_, 2, false, false)                                             \
+    if constexpr (G_ == 1) {                                                                          \
+        QNN_STREAM_L(V_, WM_, WN_, WCH_, 1, 2, false, true)                                           \
+    }
+#define QNN_STREAM_1(V_, WM_, WN_, WCH_, G_)                                                          \
+    QNN_STREAM_L(V_, WM_, WN_, WCH_, G_, 2, true, false)                                              \
+    if constexpr (G_ == 1) {                                                                          \
+        QNN_STREAM_L(V_, WM_, WN_, WCH_, 1, 2, true, true)                                            \
+    }                                                                                                 \
+    QNN_STREAM_L(V_, WM_, WN_, WCH_, G_, 1, true, false)                                              \
+    QNN_STREAM_L(V_, WM_, WN_, WCH_, G_, 0, true, false)
     if constexpr (PART == 0) {
         QNN_STREAM_VARIANTS(QNN_STREAM_0)
     } else {

@@ -552,12 +552,12 @@ bool plan_img(ImgArgs &p, const qnn_tensor *x, int32_t m, const qnn_conv_geom *g
 // stride and padding; a filter over the whole image and pointwise layers run
 // as one-pixel images (a plain matrix product).
 struct StreamTile {
-    int wm, wn, wch;
+    int wm, wn, wch, g;
     bool tail;  // built for narrow and odd pixels too
 };
-#define QNN_STREAM_HAS(V_, WM_, WN_, WCH_) v == V_ ||
+#define QNN_STREAM_HAS(V_, WM_, WN_, WCH_, G_) v == V_ ||
 constexpr bool stream_tail_built(int v) { return QNN_STREAM_VARIANTS_TAIL(QNN_STREAM_HAS) false; }
-#define QNN_STREAM_TILE(V_, WM_, WN_, WCH_) {WM_, WN_, WCH_, stream_tail_built(V_)},
+#define QNN_STREAM_TILE(V_, WM_, WN_, WCH_, G_) {WM_, WN_, WCH_, G_, stream_tail_built(V_)},
 constexpr StreamTile kStreamTiles[] = {QNN_STREAM_VARIANTS(QNN_STREAM_TILE)};
 #undef QNN_STREAM_TILE
 #undef QNN_STREAM_HAS
@@ -643,7 +643,7 @@ bool plan_stream(StreamArgs &best, int &variant, const qnn_tensor *x, int32_t m,
     const int nv = (int)(sizeof(kStreamTiles) / sizeof(kStreamTiles[0]));
     for (int v = 0; v < nv; ++v) {
         const StreamTile &T = kStreamTiles[v];
-        if ((a.lg < 2 || a.tail) && !T.tail)
+        if (((a.lg < 2 || a.tail) && !T.tail) || (a.pw1 && T.g != 1))
             continue;
         const int MT = 32 * T.wm * T.wch, PT = 32 * T.wn * (4 / T.wch);
         const int64_t Q = pool ? PT / 4 : PT;
@@ -678,7 +678,7 @@ bool plan_stream(StreamArgs &best, int &variant, const qnn_tensor *x, int32_t m,
         c.off_out = (int32_t)off;
         const int64_t out_bytes = e->kind == QNN_EPI_RAW32 ? 0 : (pool ? Q * (MT + 16) : Q * (MT * bits / 8 + 4));
         const int64_t out_end = off + out_bytes;
-        off += 2 * MT * 80;
+        off += 2 * MT * (64 * T.g + 16);
         c.off_x = (int32_t)off;
         c.xbuf = (int32_t)(nslots * ps);
         off += (int64_t)(a.pw1 ? 2 : 1) * c.xbuf;
@@ -710,8 +710,9 @@ bool plan_stream(StreamArgs &best, int &variant, const qnn_tensor *x, int32_t m,
         double thr = mfma > lds ? mfma : lds;
         if (glob > thr)
             thr = glob;
-        const double lat = mfma + 700.0;
-        const double per = thr * conc > lat ? thr * conc : lat;
+        // (two slices per step wait half as often)
+        const double lat = mfma + (T.g == 2 ? 450.0 : 700.0);
+        const double per = (thr * conc > lat ? thr * conc : lat) + (T.g == 2 ? 0.0 : 40.0);
         const double cost = (double)((units + kPlanCus * conc - 1) / (kPlanCus * conc)) *
                             (steps * per + 3000.0 + conc * (PT * MT * 0.06 + nslots * rb / 32.0));
         if (variant < 0 || cost < best_cost) {

@@ -138,14 +138,16 @@ struct StreamArgs {
     FastDiv div_wo, div_ho, div_hwd, div_hv, div_mt, div_kw;
 };
 
-// Wave tiles of conv_stream_kernel: index, 32-channel and 32-output matrix
-// tiles per wave, waves along the channels (of four).
+// Tiles of conv_stream_kernel: index, 32-channel and 32-output matrix tiles per
+// wave, waves along the channels (of four), filter slices per step.
 #define QNN_STREAM_VARIANTS(X) \
-    X(0, 2, 4, 2) X(1, 2, 3, 2) X(2, 2, 2, 2) X(3, 2, 2, 1) \
-    X(4, 2, 1, 1) X(5, 1, 2, 1) X(6, 1, 1, 1) X(7, 1, 1, 2)
+    X(0, 2, 4, 2, 1) X(1, 2, 2, 2, 1) X(2, 2, 2, 1, 1) X(3, 2, 2, 1, 2) \
+    X(4, 1, 2, 1, 1) X(5, 1, 2, 1, 2) X(6, 1, 1, 1, 1) X(7, 1, 1, 1, 2) \
+    X(8, 1, 1, 2, 1)
 // ... and of its instances for narrow or odd pixels (LG < 2, TAIL)
 #define QNN_STREAM_VARIANTS_TAIL(X) \
-    X(0, 2, 4, 2) X(2, 2, 2, 2) X(3, 2, 2, 1) X(5, 1, 2, 1) X(6, 1, 1, 1)
+    X(0, 2, 4, 2, 1) X(1, 2, 2, 2, 1) X(2, 2, 2, 1, 1) X(3, 2, 2, 1, 2) \
+    X(4, 1, 2, 1, 1) X(5, 1, 2, 1, 2) X(6, 1, 1, 1, 1) X(7, 1, 1, 1, 2)
 
 // Arguments of the INT-1 XNOR/popcount convolution.
 struct XnorArgs {
