@@ -12,6 +12,7 @@ less significant bits, int32 outputs for the raw epilogue.
 import ctypes
 import os
 import re
+import struct
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 # QNN_LIBRARY names another build of the same sources (the sanitizer test
@@ -61,6 +62,12 @@ class Epi(ctypes.Structure):
 
 _lib = None
 
+# The layer entry points once more, with plain pointer arguments: descriptors
+# go in as packed bytes.  A call through ctypes structures takes longer on the
+# host than most layers run on the device (building them, asking the library
+# for the output shape, a stream object: 13 us a call, launch included).
+_raw = {}
+
 
 def lib():
     """Load libqnn.so (raises if it has not been built)."""
@@ -105,6 +112,16 @@ def lib():
         L.qnn_pack_host.argtypes = [P, ctypes.c_size_t, ctypes.c_int32, P]
         L.qnn_unpack_host.restype = ctypes.c_int
         L.qnn_unpack_host.argtypes = [P, ctypes.c_size_t, ctypes.c_int32, ctypes.c_int32, P]
+        I = ctypes.c_int32
+        for name, args in (("qnn_conv2d", [P, P, I, P, P, P, P, P, P]),
+                           ("qnn_conv2d_tiled", [P, P, I, P, P, P, P, P, P, P]),
+                           ("qnn_conv2d_maxpool", [P, P, I, P, P, P, I, I, P, P, P]),
+                           ("qnn_linear", [P, P, I, P, P, P, P, P]),
+                           ("qnn_maxpool2d", [P, P, I, I, I, I, P, P, P])):
+            f = L[name]  # a function object of its own
+            f.restype = ctypes.c_int
+            f.argtypes = args
+            _raw[name] = f
         _lib = L
     return _lib
 
@@ -126,10 +143,61 @@ def _ptr(t):
     return None if t is None else ctypes.c_void_p(t.data_ptr())
 
 
-def _stream(stream):
-    import torch
-    s = torch.cuda.current_stream() if stream is None else stream
-    return ctypes.c_void_p(s.cuda_stream)
+def _call(name, *args):
+    f = _raw.get(name)
+    if f is None:
+        lib()
+        f = _raw[name]
+    status = f(*args)
+    if status != 0:
+        raise QnnError(status, name)
+
+
+_current = None  # () -> torch's current stream on the current device, as an integer
+
+
+def _stream_int(stream):
+    global _current
+    if stream is not None:
+        return stream.cuda_stream
+    if _current is None:
+        import torch
+        raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+        if raw is None:
+            _current = lambda: torch.cuda.current_stream().cuda_stream
+        else:
+            device = torch.cuda.current_device
+            _current = lambda: raw(device())
+    return _current()
+
+
+_pack5 = struct.Struct("@5i").pack
+_pack6 = struct.Struct("@6i").pack
+_pack_epi = struct.Struct("@i4x4P2i").pack
+
+
+def _tensor_bytes(n, h, w, c, bits):
+    try:
+        return _pack5(n, h, w, c, bits)
+    except struct.error:  # a value past 32 bits: as the structure takes it
+        return bytes(Tensor(n, h, w, c, bits))
+
+
+def _geom_bytes(kh, kw, stride, pad):
+    try:
+        return _pack6(kh, kw, stride[0], stride[1], pad[0], pad[1])
+    except struct.error:
+        return bytes(ConvGeom(kh, kw, stride[0], stride[1], pad[0], pad[1]))
+
+
+def _epi_bytes(kind, bias, mult, shift, thresh, clip):
+    try:
+        return _pack_epi(kind, bias.data_ptr() if bias is not None else 0,
+                         mult.data_ptr() if mult is not None else 0,
+                         shift.data_ptr() if shift is not None else 0,
+                         thresh.data_ptr() if thresh is not None else 0, clip[0], clip[1])
+    except struct.error:
+        return bytes(_epi(kind, bias, mult, shift, thresh, clip)[0])
 
 
 def _epi(kind, bias, mult, shift, thresh, clip):
@@ -155,6 +223,41 @@ def out_shape(xshape, bits, m, kh, kw, stride=(1, 1), pad=(0, 0), epi="requant")
     return (y.n, y.h, y.w, y.c, y.bits)
 
 
+def _conv_shape(xshape, bits, m, kh, kw, stride, pad, kind):
+    """out_shape, worked out here for every layer the library accepts; the
+    others go to the library, which refuses them."""
+    n, h, w, c = xshape
+    if kh >= 1 and kw >= 1 and stride[0] >= 1 and stride[1] >= 1 and pad[0] >= 0 and pad[1] >= 0:
+        ho = (h + 2 * pad[0] - kh) // stride[0] + 1
+        wo = (w + 2 * pad[1] - kw) // stride[1] + 1
+        if ho >= 1 and wo >= 1 and n >= 0 and h >= 1 and w >= 1 and c >= 1 and m >= 1:
+            obits = bits if kind == EPI_REQUANT or kind == EPI_STAIR else (1 if kind == EPI_THRESH1 else 32)
+            # (sizes near the library's limits are the library's to judge)
+            if bits in (8, 4, 2, 1) and n * h * w * c < 1 << 40 and n * ho * wo * m < 1 << 40:
+                return (n, ho, wo, m, obits)
+    return out_shape(xshape, bits, m, kh, kw, stride, pad, kind)
+
+
+def _new_out(shape, out, x):
+    """_out_tensor, without its detour where x is what it usually is."""
+    if out is None:
+        n, h, w, c, bits = shape
+        if bits != 32 and x.dtype is _uint8():
+            return x.new_empty((n, h, w, (c * bits + 7) // 8))
+    return _out_tensor(shape, out, x.device)
+
+
+_u8 = None
+
+
+def _uint8():
+    global _u8
+    if _u8 is None:
+        import torch
+        _u8 = torch.uint8
+    return _u8
+
+
 def _out_tensor(shape, out, device):
     import torch
     n, h, w, c, bits = shape
@@ -178,20 +281,18 @@ def conv2d(x, xshape, bits, w, m, kh, kw, stride=(1, 1), pad=(0, 0), epi="requan
     uint8 [N, Ho, Wo, out bytes] codes or int32 [N, Ho, Wo, M] (raw32).
     tile = (kernel, tile_m, tile_n, waves) picks the tile shape
     (qnn_conv2d_tiled) instead of the library."""
-    yshape = out_shape(xshape, bits, m, kh, kw, stride, pad, epi)
-    y = _out_tensor(yshape, out, x.device)
-    e, _ = _epi(epi, bias, mult, shift, thresh, clip)
-    xd = Tensor(*xshape, bits)
-    yd = Tensor(*yshape)
-    g = ConvGeom(kh, kw, stride[0], stride[1], pad[0], pad[1])
+    kind = _EPI_NAMES[epi] if isinstance(epi, str) else epi
+    yshape = _conv_shape(xshape, bits, m, kh, kw, stride, pad, kind)
+    y = _new_out(yshape, out, x)
+    xd = _tensor_bytes(*xshape, bits)
+    yd = _tensor_bytes(*yshape)
+    g = _geom_bytes(kh, kw, stride, pad)
+    e = _epi_bytes(kind, bias, mult, shift, thresh, clip)
     if tile is None:
-        _check(lib().qnn_conv2d(ctypes.byref(xd), _ptr(x), m, _ptr(w), ctypes.byref(g),
-                                ctypes.byref(e), ctypes.byref(yd), _ptr(y), _stream(stream)), "qnn_conv2d")
+        _call("qnn_conv2d", xd, x.data_ptr(), m, w.data_ptr(), g, e, yd, y.data_ptr(), _stream_int(stream))
     else:
-        t = Tile(*tile)
-        _check(lib().qnn_conv2d_tiled(ctypes.byref(xd), _ptr(x), m, _ptr(w), ctypes.byref(g),
-                                      ctypes.byref(e), ctypes.byref(t), ctypes.byref(yd), _ptr(y),
-                                      _stream(stream)), "qnn_conv2d_tiled")
+        _call("qnn_conv2d_tiled", xd, x.data_ptr(), m, w.data_ptr(), g, e, bytes(Tile(*tile)), yd, y.data_ptr(),
+              _stream_int(stream))
     return y
 
 
@@ -199,16 +300,13 @@ def conv2d_maxpool(x, xshape, bits, w, m, kh, kw, stride=(1, 1), pad=(0, 0), epi
                    bias=None, mult=None, shift=None, thresh=None, clip=(0, 0), out=None, stream=None):
     """Convolution fused with 2x2 / stride-2 max-pooling (qnn_conv2d_maxpool).
     Returns uint8 [N, floor(Ho/2), floor(Wo/2), out bytes] codes."""
-    n, ho, wo, c, obits = out_shape(xshape, bits, m, kh, kw, stride, pad, epi)
+    kind = _EPI_NAMES[epi] if isinstance(epi, str) else epi
+    n, ho, wo, c, obits = _conv_shape(xshape, bits, m, kh, kw, stride, pad, kind)
     yshape = (n, ho // 2, wo // 2, c, obits)
-    y = _out_tensor(yshape, out, x.device)
-    e, _ = _epi(epi, bias, mult, shift, thresh, clip)
-    xd = Tensor(*xshape, bits)
-    yd = Tensor(*yshape)
-    g = ConvGeom(kh, kw, stride[0], stride[1], pad[0], pad[1])
-    _check(lib().qnn_conv2d_maxpool(ctypes.byref(xd), _ptr(x), m, _ptr(w), ctypes.byref(g),
-                                    ctypes.byref(e), 2, 2, ctypes.byref(yd), _ptr(y), _stream(stream)),
-           "qnn_conv2d_maxpool")
+    y = _new_out(yshape, out, x)
+    _call("qnn_conv2d_maxpool", _tensor_bytes(*xshape, bits), x.data_ptr(), m, w.data_ptr(),
+          _geom_bytes(kh, kw, stride, pad), _epi_bytes(kind, bias, mult, shift, thresh, clip), 2, 2,
+          _tensor_bytes(*yshape), y.data_ptr(), _stream_int(stream))
     return y
 
 
@@ -218,12 +316,10 @@ def linear(x, xshape, bits, w, m, epi="raw32", bias=None, mult=None, shift=None,
     kind = _EPI_NAMES[epi] if isinstance(epi, str) else epi
     obits = {EPI_REQUANT: bits, EPI_THRESH1: 1, EPI_RAW32: 32}[kind]
     yshape = (xshape[0], 1, 1, m, obits)
-    y = _out_tensor(yshape, out, x.device)
-    e, _ = _epi(kind, bias, mult, shift, thresh, clip)
-    xd = Tensor(*xshape, bits)
-    yd = Tensor(*yshape)
-    _check(lib().qnn_linear(ctypes.byref(xd), _ptr(x), m, _ptr(w), ctypes.byref(e),
-                            ctypes.byref(yd), _ptr(y), _stream(stream)), "qnn_linear")
+    y = _new_out(yshape, out, x)
+    _call("qnn_linear", _tensor_bytes(*xshape, bits), x.data_ptr(), m, w.data_ptr(),
+          _epi_bytes(kind, bias, mult, shift, thresh, clip), _tensor_bytes(*yshape), y.data_ptr(),
+          _stream_int(stream))
     return y
 
 
@@ -233,11 +329,9 @@ def maxpool2d(x, xshape, bits, kh, kw, sh, sw, out=None, stream=None):
     ho = (h - kh) // sh + 1
     wo = (w_ - kw) // sw + 1
     yshape = (n, ho, wo, c, bits)
-    y = _out_tensor(yshape, out, x.device)
-    xd = Tensor(*xshape, bits)
-    yd = Tensor(*yshape)
-    _check(lib().qnn_maxpool2d(ctypes.byref(xd), _ptr(x), kh, kw, sh, sw, ctypes.byref(yd),
-                               _ptr(y), _stream(stream)), "qnn_maxpool2d")
+    y = _new_out(yshape, out, x)
+    _call("qnn_maxpool2d", _tensor_bytes(*xshape, bits), x.data_ptr(), kh, kw, sh, sw, _tensor_bytes(*yshape),
+          y.data_ptr(), _stream_int(stream))
     return y
 
 
@@ -245,7 +339,7 @@ def relu_s8(x, out=None, stream=None):
     """Signed 8-bit ReLU (qnn_relu_s8); out may be x (in place)."""
     import torch
     y = torch.empty_like(x) if out is None else out
-    _check(lib().qnn_relu_s8(_ptr(x), _ptr(y), x.numel(), _stream(stream)), "qnn_relu_s8")
+    _check(lib().qnn_relu_s8(x.data_ptr(), y.data_ptr(), x.numel(), _stream_int(stream)), "qnn_relu_s8")
     return y
 
 
