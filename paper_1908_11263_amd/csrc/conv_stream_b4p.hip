@@ -1,0 +1,12 @@
+// 4-bit convolution: instantiations of the streaming implicit-GEMM kernel
+// (int8 matrix cores), packed input tiles.
+#include "conv_stream_impl.h"
+
+namespace qnn {
+
+hipError_t launch_conv_stream_b4p(const StreamArgs &a, int variant, hipStream_t s)
+{
+    return launch_conv_stream_bits<4, 0, true>(a, variant, s);
+}
+
+}  // namespace qnn

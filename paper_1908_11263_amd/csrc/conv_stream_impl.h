@@ -153,10 +153,21 @@ enum { STREAM_CODES = 0, STREAM_RAW = 1, STREAM_POOL = 2 };
 // stored after its last (batches past the second are loaded there).
 // G: filter slices per step (between two barriers).  Two save 3-8% unless their
 // LDS costs a workgroup of a compute unit.
-template <int BITS, int WM, int WN, int WCH, int G, int MODE, int LG, bool TAIL, bool PW>
+// XP (4 bits, LG = 2): the input tile stays packed in LDS and its fragments (8
+// packed bytes per lane) are unpacked in registers, six instructions beside WM
+// matrix instructions of 32 clocks.  Half the LDS per pixel, which is what
+// limits the workgroups of a compute unit where strides, tall filters or short
+// images make the tile many rows: INT-4 56x56x64 -> 128, stride 2, staircase,
+// batch 256, 65.4 -> 49.3 us; 8x30x56 -> 16, pooled, batch 12222, 190 -> 125.
+// Where no more workgroups fit it costs up to 7%, except with one-tap filters,
+// whose input is read once: 1x1 56x22x64 -> 34, stride 2, pooled, batch 3005,
+// 28.8 -> 19.9 us, so these are built packed only.  2- and 1-bit codes take more instructions
+// per fragment and feed matrix instructions of half the length: not built.
+template <int BITS, int WM, int WN, int WCH, int G, int MODE, int LG, bool TAIL, bool PW, bool XP>
 __global__ void __launch_bounds__(256, (WM * WN >= 6 ? 2 : (WM * WN >= 4 ? 3 : 4))) conv_stream_kernel(StreamArgs a)
 {
     extern __shared__ __align__(16) uint8_t smem[];
+    static_assert(!XP || (BITS == 4 && LG == 2), "packed tiles: whole 4-bit blocks");
     static_assert(!PW || G == 1, "one-tap filters bring new input with every slice");
     constexpr bool F4 = BITS <= 2;
     constexpr int WPX = 4 / WCH;
@@ -169,8 +180,10 @@ __global__ void __launch_bounds__(256, (WM * WN >= 6 ? 2 : (WM * WN >= 4 ? 3 : 4
     constexpr int IPR = TPS * QPR;                  // filter items per row and step
     constexpr int D = 3 - G;                         // filter loads are issued D steps ahead
     constexpr int WS = 64 * G + 16;                 // LDS strides: odd multiples of 16 bytes
-    constexpr int PS = LG == 2 ? 80 : (LG == 1 ? 48 : 16);
-    constexpr int SPX = (16 << LG) / QPR;           // staged bytes of an input item
+    constexpr int XD = XP ? 2 : 1;                  // staged bytes per byte held
+    // (LDS strides that no two lanes of a half-wave's fragment read share banks at)
+    constexpr int PS = XP ? 40 : (LG == 2 ? 80 : (LG == 1 ? 48 : 16));
+    constexpr int SPX = (16 << LG) / QPR / XD;      // bytes of an input item in LDS
     constexpr int UW = (MT * IPR + 255) / 256;      // filter items per thread and step
     // input items per thread and batch
     constexpr int UX = PW ? (PT * QPR + 255) / 256 : 4;
@@ -378,9 +391,15 @@ __global__ void __launch_bounds__(256, (WM * WN >= 6 ? 2 : (WM * WN >= 4 ? 3 : 4
             if (!PW && first >= nslots * QPR)
                 break;
             const int slot = (int)((uint32_t)(first + tid) / QPR);
-            if (slot < nslots)
-                stream_store<BITS, F4, false, LB>(sX + slot * PS, q[u], 4);
-            if (BITS != 8)
+            if (slot < nslots) {
+                if constexpr (XP) {
+                    *(uint2 *)(sX + slot * PS) = make_uint2(q[u].x, q[u].y);
+                    *(uint2 *)(sX + slot * PS + 8) = make_uint2(q[u].z, q[u].w);
+                } else {
+                    stream_store<BITS, F4, false, LB>(sX + slot * PS, q[u], 4);
+                }
+            }
+            if (BITS != 8 && !XP)
                 __builtin_amdgcn_sched_barrier(0);  // (unpacked together they would spill)
         }
     };
@@ -445,9 +464,9 @@ __global__ void __launch_bounds__(256, (WM * WN >= 6 ? 2 : (WM * WN >= 4 ? 3 : 4
         }
         const int vr = PW ? 0 : (nn - n0) * a.hv + oy * a.ssh - v0;
         if (PW)
-            base[c] = (wpx * 32 * WN + c * 32 + r32) * PS + a.off_x + h * 16;
+            base[c] = (wpx * 32 * WN + c * 32 + r32) * PS + a.off_x + h * (16 / XD);
         else
-            base[c] = (vr * a.hwd + (a.ssw == 2 ? ox : ox * a.ssw)) * PS + a.off_x + (LG > 0 ? h * 16 : 0);
+            base[c] = (vr * a.hwd + (a.ssw == 2 ? ox : ox * a.ssw)) * PS + a.off_x + (LG > 0 ? h * (16 / XD) : 0);
     }
     const int wlane = (wch * 32 * WM + r32) * WS + h * 16;
 
@@ -487,10 +506,10 @@ __global__ void __launch_bounds__(256, (WM * WN >= 6 ? 2 : (WM * WN >= 4 ? 3 : 4
     auto x_offs = [&](int cb, int t, int &o0, int &o1) {
         if (PW) {
             o0 = (cb & 1) * a.xbuf;
-            o1 = o0 + 32;
+            o1 = o0 + 32 / XD;
         } else if (LG == 2) {
             o0 = __builtin_amdgcn_readlane(tapv, t);
-            o1 = o0 + 32;
+            o1 = o0 + 32 / XD;
         } else if (LG == 1) {
             o0 = __builtin_amdgcn_readlane(tapv, 2 * t);
             o1 = __builtin_amdgcn_readlane(tapv, 2 * t + 1);
@@ -527,15 +546,28 @@ __global__ void __launch_bounds__(256, (WM * WN >= 6 ? 2 : (WM * WN >= 4 ? 3 : 4
             x_offs(cb, sl, o0, o1);
             const uint8_t *wp = smem + rb + wlane + 64 * g;
             v4i xf[2][WN], wf[2][WM];
+            uint2 xp[2][WN];
             auto frags = [&](int ks) {
 #pragma unroll
                 for (int i = 0; i < WM; ++i)
                     wf[ks][i] = *(const v4i *)(wp + i * 32 * WS + ks * 32);
 #pragma unroll
-                for (int c = 0; c < WN; ++c)
-                    xf[ks][c] = *(const v4i *)(smem + base[c] + (ks ? o1 : o0));
+                for (int c = 0; c < WN; ++c) {
+                    if constexpr (XP)
+                        xp[ks][c] = *(const uint2 *)(smem + base[c] + (ks ? o1 : o0));
+                    else
+                        xf[ks][c] = *(const v4i *)(smem + base[c] + (ks ? o1 : o0));
+                }
             };
             auto mfmas = [&](int ks) {
+                if constexpr (XP) {
+#pragma unroll
+                    for (int c = 0; c < WN; ++c) {
+                        const uint2 d = xp[ks][c];
+                        xf[ks][c] = (v4i){(int)(d.x & 0x0F0F0F0Fu), (int)((d.x >> 4) & 0x0F0F0F0Fu),
+                                          (int)(d.y & 0x0F0F0F0Fu), (int)((d.y >> 4) & 0x0F0F0F0Fu)};
+                    }
+                }
 #pragma unroll
                 for (int i = 0; i < WM; ++i)
 #pragma unroll
@@ -1079,15 +1111,16 @@ __global__ void __launch_bounds__(256, (WM * WN >= 6 ? 2 : (WM * WN >= 4 ? 3 : 4
     }
 }
 
-// Part 0: one tap per step, whole items; part 1: the others.
-template <int BITS, int PART>
+// Part 0: one tap per step, whole items; part 1: the others.  XP: packed input
+// tiles (one tap per step).
+template <int BITS, int PART, bool XP = false>
 hipError_t launch_conv_stream_bits(const StreamArgs &a, int variant, hipStream_t s)
 {
     const int mode = a.pool ? STREAM_POOL : (a.epi == EPI_RAW32 ? STREAM_RAW : STREAM_CODES);
     const dim3 grid((unsigned)(a.ptiles * a.mtiles));
 #define QNN_STREAM_M(V_, WM_, WN_, WCH_, G_, MODE_, LG_, TAIL_, PW_)                                  \
     if (variant == V_ && mode == MODE_ && a.lg == LG_ && a.pw1 == PW_) {                              \
-        auto *k = conv_stream_kernel<BITS, WM_, WN_, WCH_, G_, MODE_, LG_, TAIL_, PW_>;               \
+        auto *k = conv_stream_kernel<BITS, WM_, WN_, WCH_, G_, MODE_, LG_, TAIL_, PW_, XP>;               \
         if (a.lds_bytes > 64 * 1024 &&                                                                \
             hipFuncSetAttribute((const void *)k, hipFuncAttributeMaxDynamicSharedMemorySize,          \
                                 160 * 1024) != hipSuccess)                                            \
@@ -1101,19 +1134,21 @@ hipError_t launch_conv_stream_bits(const StreamArgs &a, int variant, hipStream_t
     if constexpr (BITS != 1) {                                                                        \
         QNN_STREAM_M(V_, WM_, WN_, WCH_, G_, STREAM_POOL, LG_, TAIL_, PW_)                            \
     }
-    // one-tap filters (of one tap per step): G = 1 only
+    // one-tap filters (of one tap per step): G = 1 only, packed at 4 bits
 #define QNN_STREAM_0(V_, WM_, WN_, WCH_, G_)                                                          \
     QNN_STREAM_L(V_, WM_, WN_, WCH_, G_, 2, false, false)                                             \
-    if constexpr (G_ == 1) {                                                                          \
+    if constexpr (G_ == 1 && (XP || BITS != 4)) {                                                     \
         QNN_STREAM_L(V_, WM_, WN_, WCH_, 1, 2, false, true)                                           \
     }
 #define QNN_STREAM_1(V_, WM_, WN_, WCH_, G_)                                                          \
     QNN_STREAM_L(V_, WM_, WN_, WCH_, G_, 2, true, false)                                              \
-    if constexpr (G_ == 1) {                                                                          \
+    if constexpr (G_ == 1 && (XP || BITS != 4)) {                                                     \
         QNN_STREAM_L(V_, WM_, WN_, WCH_, 1, 2, true, true)                                            \
     }                                                                                                 \
-    QNN_STREAM_L(V_, WM_, WN_, WCH_, G_, 1, true, false)                                              \
-    QNN_STREAM_L(V_, WM_, WN_, WCH_, G_, 0, true, false)
+    if constexpr (!XP) {                                                                              \
+        QNN_STREAM_L(V_, WM_, WN_, WCH_, G_, 1, true, false)                                          \
+        QNN_STREAM_L(V_, WM_, WN_, WCH_, G_, 0, true, false)                                          \
+    }
     if constexpr (PART == 0) {
         QNN_STREAM_VARIANTS(QNN_STREAM_0)
     } else {

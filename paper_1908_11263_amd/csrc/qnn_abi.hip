@@ -629,7 +629,6 @@ bool plan_stream(StreamArgs &best, int &variant, const qnn_tensor *x, int32_t m,
     a.tail = lb != run ? 1 : 0;
     a.dw = lb % ib != 0 ? 1 : 0;
     a.pw1 = taps == 1 && a.lg == 2 ? 1 : 0;
-    const int ps = a.lg == 2 ? 80 : (a.lg == 1 ? 48 : 16);
     a.div_wo = make_fastdiv((uint32_t)a.wo);
     a.div_ho = make_fastdiv((uint32_t)a.ho);
     a.div_hwd = make_fastdiv((uint32_t)hwd);
@@ -641,8 +640,13 @@ bool plan_stream(StreamArgs &best, int &variant, const qnn_tensor *x, int32_t m,
     double best_cost = 0;
     variant = -1;
     const int nv = (int)(sizeof(kStreamTiles) / sizeof(kStreamTiles[0]));
-    for (int v = 0; v < nv; ++v) {
+    // every tile, then (4 bits) every tile with its input kept packed
+    for (int vx = 0; vx < (bits == 4 && a.lg == 2 ? 2 * nv : nv); ++vx) {
+        const int v = vx % nv, xp = vx / nv;
+        const int ps = xp ? 40 : (a.lg == 2 ? 80 : (a.lg == 1 ? 48 : 16));  // bytes of a pixel in LDS
         const StreamTile &T = kStreamTiles[v];
+        if (bits == 4 && a.pw1 && !xp)
+            continue;  // (one-tap filters: packed only)
         if (((a.lg < 2 || a.tail) && !T.tail) || (a.pw1 && T.g != 1))
             continue;
         const int MT = 32 * T.wm * T.wch, PT = 32 * T.wn * (4 / T.wch);
@@ -664,6 +668,7 @@ bool plan_stream(StreamArgs &best, int &variant, const qnn_tensor *x, int32_t m,
             nslots * ps > kLdsBytes)
             continue;
         StreamArgs c = a;
+        c.xp = xp;
         c.nslots = (int32_t)nslots;
         c.nbatch = (int32_t)((nslots * (run / ib) + 1023) / 1024);
         int64_t off = 0;
@@ -712,7 +717,9 @@ bool plan_stream(StreamArgs &best, int &variant, const qnn_tensor *x, int32_t m,
             thr = glob;
         // (two slices per step wait half as often)
         const double lat = mfma + (T.g == 2 ? 450.0 : 700.0);
-        const double per = (thr * conc > lat ? thr * conc : lat) + (T.g == 2 ? 0.0 : 40.0);
+        // (packed input is unpacked at every fragment: measured 1-7%, where the
+        // tile and the workgroups of a compute unit are the same)
+        const double per = ((thr * conc > lat ? thr * conc : lat) + (T.g == 2 ? 0.0 : 40.0)) * (xp && !a.pw1 ? 1.06 : 1.0);
         const double cost = (double)((units + kPlanCus * conc - 1) / (kPlanCus * conc)) *
                             (steps * per + 3000.0 + conc * (PT * MT * 0.06 + nslots * rb / 32.0));
         if (variant < 0 || cost < best_cost) {
@@ -736,6 +743,9 @@ qnn_status run_stream(StreamArgs &a, int variant, int bits, const void *x_dev, c
     a.shift = e->shift;
     a.thresh = e->thresh;
     a.ypb = ypb;
+    if (a.xp)
+        return (a.tail ? launch_conv_stream_b4px : launch_conv_stream_b4p)(a, variant, s) == hipSuccess
+                   ? QNN_OK : QNN_ERR_LAUNCH;
     hipError_t (*const launch[4][2])(const StreamArgs &, int, hipStream_t) = {
         {launch_conv_stream_b1, launch_conv_stream_b1x},
         {launch_conv_stream_b2, launch_conv_stream_b2x},

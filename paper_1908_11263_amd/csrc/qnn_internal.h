@@ -133,6 +133,7 @@ struct StreamArgs {
     int32_t last2;         // the last block's (lg < 2: last step's) second half holds data
     int32_t nbatch;        // input batches of a block
     int32_t tail, dw;      // the last block is not full; it ends inside an item (loaded by words)
+    int32_t xp;            // the input tile stays packed (4 bits, lg = 2)
     int32_t ptiles, mtiles;
     int32_t off_epi, off_sum, off_pix, off_w, off_x, off_out, xbuf, lds_bytes;
     FastDiv div_wo, div_ho, div_hwd, div_hv, div_mt, div_kw;
@@ -187,6 +188,8 @@ hipError_t launch_conv_stream_b8(const StreamArgs &a, int variant, hipStream_t s
 hipError_t launch_conv_stream_b8x(const StreamArgs &a, int variant, hipStream_t s);
 hipError_t launch_conv_stream_b4(const StreamArgs &a, int variant, hipStream_t s);
 hipError_t launch_conv_stream_b4x(const StreamArgs &a, int variant, hipStream_t s);
+hipError_t launch_conv_stream_b4p(const StreamArgs &a, int variant, hipStream_t s);
+hipError_t launch_conv_stream_b4px(const StreamArgs &a, int variant, hipStream_t s);
 hipError_t launch_conv_stream_b2(const StreamArgs &a, int variant, hipStream_t s);
 hipError_t launch_conv_stream_b2x(const StreamArgs &a, int variant, hipStream_t s);
 hipError_t launch_conv_stream_b1(const StreamArgs &a, int variant, hipStream_t s);

@@ -81,6 +81,20 @@ def test_tiles_and_strides(qnn, orc, bits):
             compare(gpu_pool(qnn, L), oracle_pool(orc, L), "%s case %d pooled" % (L.name, i))
 
 
+@pytest.mark.parametrize("epi", ["requant", "raw32", "stair", "pool"])
+def test_packed_input_tiles(qnn, orc, epi):
+    """4-bit layers whose input tiles stay packed in local memory because more
+    workgroups fit (whole and odd blocks; one-tap filters always do)."""
+    for i, (n, h, w, c, m, k, s) in enumerate([
+            (137, 13, 70, 64, 72, 3, 2), (46, 40, 41, 64, 40, 5, 2), (94, 40, 41, 88, 40, 3, 2),
+            (87, 40, 41, 64, 130, 1, 1), (63, 20, 41, 88, 130, 1, 2), (40, 11, 9, 72, 34, 1, 1)]):
+        L = layer(4, n, h, w, c, m, k, stride=s, seed=60 + i, epi="requant" if epi == "pool" else epi)
+        if epi == "pool":
+            compare(gpu_pool(qnn, L), oracle_pool(orc, L), "packed case %d pooled" % i)
+        else:
+            compare(gpu_conv(L), oracle_conv(orc, L), "packed case %d %s" % (i, epi))
+
+
 @pytest.mark.parametrize("bits", [8, 4, 2])
 def test_plan_forms(qnn, orc, bits):
     """Multipliers and shifts of each form of the compression: 32-bit, 64-bit,
