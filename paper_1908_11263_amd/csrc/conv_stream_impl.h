@@ -34,8 +34,8 @@
 // (and XNOR / popcount at 1 bit): 256 images of 14x14x256 INT-8 codes, 256 3x3
 // filters, 151 -> 38.7 us (1.5 POP/s); INT-1 8x8x256, 256 3x3 filters, batch
 // 1024, 87 -> 20.0 us; 1x1 INT-8 28x28x128 -> 256, batch 256, 65.8 -> 30.7 us;
-// INT-4 56x56x64 -> 128, stride 2, staircase, batch 256, 84.6 -> 65.4 us;
-// 1000x4096 by 4096x1000 INT-8 58 -> 19.7 us.  What bounds it: where K is long,
+// INT-4 56x56x64 -> 128, stride 2, staircase, batch 256, 84.6 -> 49.3 us;
+// 1000x4096 by 4096x1000 INT-8 58 -> 18.5 us.  What bounds it: where K is long,
 // the main loop (a 2x4 wave tile's step of 64 K bytes is 512 clocks of MFMAs;
 // with the fragment reads, slice stores and the barrier the loop runs at
 // 60-70% of the matrix rate with two workgroups per compute unit); where K is
@@ -147,7 +147,7 @@ enum { STREAM_CODES = 0, STREAM_RAW = 1, STREAM_POOL = 2 };
 // 1, 0: pixels of one block of at most 32 / 16 staged bytes, two / four taps
 // per step).  TAIL: the last block's items may end inside their 16 bytes.
 // PW: filters of one tap (LG = 2): a slot is an output of the tile, and both
-// operands stream, the input in two LDS buffers loaded two steps ahead.
+// operands stream, the input in two LDS buffers loaded D steps ahead.
 // Otherwise the input block stays for all taps in one LDS buffer; the next
 // block's loads are issued in its first two steps, held in registers and
 // stored after its last (batches past the second are loaded there).
@@ -178,7 +178,6 @@ __global__ void __launch_bounds__(256, (WM * WN >= 6 ? 2 : (WM * WN >= 4 ? 3 : 4
     constexpr int LB = RUN < 16 ? RUN : 16;         // packed bytes of an item
     constexpr int QPR = RUN / LB, TPS = 4 >> LG;    // items per run, taps per step
     constexpr int IPR = TPS * QPR;                  // filter items per row and step
-    constexpr int D = 3 - G;                         // filter loads are issued D steps ahead
     constexpr int WS = 64 * G + 16;                 // LDS strides: odd multiples of 16 bytes
     constexpr int XD = XP ? 2 : 1;                  // staged bytes per byte held
     // (LDS strides that no two lanes of a half-wave's fragment read share banks at)
@@ -187,6 +186,12 @@ __global__ void __launch_bounds__(256, (WM * WN >= 6 ? 2 : (WM * WN >= 4 ? 3 : 4
     constexpr int UW = (MT * IPR + 255) / 256;      // filter items per thread and step
     // input items per thread and batch
     constexpr int UX = PW ? (PT * QPR + 255) / 256 : 4;
+    // loads are issued D steps ahead.  One-tap filters wait for both operands
+    // in every step: four steps where the tile leaves registers for it (1000
+    // INT-8 images of 4096 codes to 1000 outputs 21.3 -> 18.5 us, 40 drawn
+    // linear layers 0.98; packed 4-bit tiles gained nothing and lost 5% on
+    // reductions of two steps)
+    constexpr int D = PW ? (UX + UW <= 3 && !XP ? 4 : 2) : 3 - G;
     // log2 of the weight scale the accumulator carries (4-bit filters are staged as 16 w)
     constexpr int SL = BITS == 4 ? 4 : 0;
     constexpr int NTH = BITS == 8 ? 1 : (1 << BITS) - 1;
@@ -249,8 +254,9 @@ __global__ void __launch_bounds__(256, (WM * WN >= 6 ? 2 : (WM * WN >= 4 ? 3 : 4
     // last one load slice 0, which is not stored.)
     auto w_load = [&](uint4 *q, int cb, int t) {
         const uint32_t so = cb < nblk && t < spb ? (uint32_t)(t * TPS * pb + cb * RB) : 0u;
-        const bool live = (TPS == 1 || t * TPS + wtap < taps) && (!TAIL || cb != lastb || nvw > 0);
-        const bool sel = TPS > 1 || TAIL;
+        const bool live = (TPS == 1 || t * TPS + wtap < taps) && (!TAIL || cb != lastb || nvw > 0) &&
+                          (!PW || D == 2 || cb < nblk);
+        const bool sel = TPS > 1 || TAIL || (PW && D > 2);
         if (TAIL && cb == lastb && a.dw) {
 #pragma unroll
             for (int u = 0; u < UW; ++u)
@@ -359,7 +365,8 @@ __global__ void __launch_bounds__(256, (WM * WN >= 6 ? 2 : (WM * WN >= 4 ? 3 : 4
     // ---- input tile: a block in batches of UX items per thread ----
     constexpr int NBPW = (PT * QPR + 256 * UX - 1) / (256 * UX);
     static_assert(!PW || NBPW == 1 || LG != 2, "a pointwise tile's block is one batch");
-    uint4 xq[2][UX];
+    constexpr int XQ = PW ? D : 2;
+    uint4 xq[XQ][UX];
     uint32_t xo[PW ? UX : 1];
     const int nbatch = PW ? 1 : a.nbatch;
     auto x_off = [&](int b, int u) {
@@ -410,7 +417,9 @@ __global__ void __launch_bounds__(256, (WM * WN >= 6 ? 2 : (WM * WN >= 4 ? 3 : 4
     }
     x_load(xq[0], 0, 0);
     if (PW) {
-        x_load(xq[1], 1, 0);
+#pragma unroll
+        for (int d = 1; d < XQ; ++d)
+            x_load(xq[d], d, 0);
     } else {
         x_load(xq[1], 0, 1);
     }
@@ -531,7 +540,7 @@ __global__ void __launch_bounds__(256, (WM * WN >= 6 ? 2 : (WM * WN >= 4 ? 3 : 4
         const int ncb = block_end ? cb + 1 : cb, nt = block_end ? 0 : t + 1;
         w_next(wq[S]);
         if (PW) {
-            x_load(xq[S & 1], cb + 2, 0);
+            x_load(xq[S % XQ], cb + D, 0);
         } else if (XL) {
             x_load(xq[0], cb + 1, 0);
             x_load(xq[1], cb + 1, 1);
@@ -594,7 +603,7 @@ __global__ void __launch_bounds__(256, (WM * WN >= 6 ? 2 : (WM * WN >= 4 ? 3 : 4
                 if (PW || nt * G + g < spb)
                     w_store(wq[(S + 1) % D] + g * UW, ncb, nt * G + g, wb + 64 * g);
             if (PW)
-                x_store(xq[(S + 1) & 1], 0, ncb & 1);
+                x_store(xq[(S + 1) % XQ], 0, ncb & 1);
         }
         stream_barrier();
         cb = ncb;
@@ -612,6 +621,14 @@ __global__ void __launch_bounds__(256, (WM * WN >= 6 ? 2 : (WM * WN >= 4 ? 3 : 4
             step(StreamInt<1>(), No());
             if (cb == nblk)
                 break;
+            if constexpr (D == 4) {
+                step(StreamInt<2>(), No());
+                if (cb == nblk)
+                    break;
+                step(StreamInt<3>(), No());
+                if (cb == nblk)
+                    break;
+            }
         }
     } else {
         for (;;) {

@@ -894,7 +894,7 @@ qnn_status run_conv(const qnn_tensor *x, const void *x_dev, int32_t m, const voi
     // tile.  Its 16x16 tiles read 32 rows of K each, about 10 MB/us in all
     // from the L2s, while the streaming kernel's time goes with its steps
     // along K (about 2 us and 0.25 us per 64 staged bytes): 1000 images of
-    // 4096 INT-8 codes to 1000 outputs, 520 MB, 59 against 22 us; 500 images
+    // 4096 INT-8 codes to 1000 outputs, 520 MB, 58 against 18.5 us; 500 images
     // of 2176 to 93, 13 MB, 4.8 against 12.3 us
     if (!force && e->kind == QNN_EPI_RAW32 && x->bits != 1 && g->kh == x->h && g->kw == x->w &&
         g->pad_h == 0 && g->pad_w == 0 && K % 64 == 0) {
