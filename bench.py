@@ -19,8 +19,8 @@ The single layers (matrix-core or latency bound) are quoted warm, the
 networks and their layers (whose first layers and classifier stream from
 HBM) cold; "us_per_step" is the quoted one, "protocol" names it.
 
-The other workloads (INT-8 batch 1, INT-2 batch 256 on the int8 and on the
-FP4 matrix path, INT-1 batch 1024 on the XNOR and on the FP4 matrix path, the
+The other workloads (INT-8 batch 1, INT-2 batch 256 and INT-1 batch 1024 on
+the library's own pick and on the forced FP4 tiles of the 32x32 kernel, the
 INT-4 layer with the staircase epilogue, the CIFAR-shaped network at INT-8
 and INT-4, batch 4096, whole and layer by layer) are reported under
 "layers".  Measured denominators (int8 matrix-core loop, XNOR/popcount loop,
@@ -756,19 +756,15 @@ def main():
             rec["us_per_step_warm"] = round(sw * 1e6, 3)
         if sc is not None:
             rec["us_per_step_cold"] = round(sc * 1e6, 3)
-        if name in ("int2_fp4", "int1_fp4"):
+        if name in ("int2", "int1", "int2_fp4", "int1_fp4"):
             rec["pct_fp4_mfma_peak"] = round(100 * 2 * step.macs / sec / 1e12 / PEAK_FP4_TFLOPS, 3)
-        if name == "int1":
-            rec["pct_xnor_valu_roofline"] = round(100 * step.macs / sec / XNOR_PEAK_BMACS, 3)
-            if calib:
-                rec["pct_xnor_measured"] = round(100 * step.macs / sec / calib["xnor"]["bmacs_per_s"], 2)
         if name == "int8" and calib:
             rec["empty_launch_us"] = calib["empty_launch_us"]
         if "cifar" in name:
             rec["images_per_s"] = round(step.net.n / sec, 1)
         if step.bytes:
             rec["algorithmic_gbs"] = round(step.bytes / sec / 1e9, 2)
-        if calib and name not in ("int1", "int1_fp4", "int2_fp4"):
+        if calib and name not in ("int2", "int1", "int1_fp4", "int2_fp4"):
             rec["pct_int8_mfma_measured"] = round(100 * 2 * step.macs / sec / 1e12 / calib["mfma_i8"]["tops"], 3)
         layers[name] = rec
         log("  %s: %.3f us/step %s (warm %s, cold %s), %.1f GMAC/s, %.2f%% of int8 MFMA peak"
