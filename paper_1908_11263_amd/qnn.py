@@ -143,6 +143,11 @@ def _ptr(t):
     return None if t is None else ctypes.c_void_p(t.data_ptr())
 
 
+def _addr(t):
+    """A tensor's address; None (NULL, the library's to accept or refuse) for None."""
+    return None if t is None else t.data_ptr()
+
+
 def _call(name, *args):
     f = _raw.get(name)
     if f is None:
@@ -289,9 +294,9 @@ def conv2d(x, xshape, bits, w, m, kh, kw, stride=(1, 1), pad=(0, 0), epi="requan
     g = _geom_bytes(kh, kw, stride, pad)
     e = _epi_bytes(kind, bias, mult, shift, thresh, clip)
     if tile is None:
-        _call("qnn_conv2d", xd, x.data_ptr(), m, w.data_ptr(), g, e, yd, y.data_ptr(), _stream_int(stream))
+        _call("qnn_conv2d", xd, x.data_ptr(), m, _addr(w), g, e, yd, y.data_ptr(), _stream_int(stream))
     else:
-        _call("qnn_conv2d_tiled", xd, x.data_ptr(), m, w.data_ptr(), g, e, bytes(Tile(*tile)), yd, y.data_ptr(),
+        _call("qnn_conv2d_tiled", xd, x.data_ptr(), m, _addr(w), g, e, bytes(Tile(*tile)), yd, y.data_ptr(),
               _stream_int(stream))
     return y
 
@@ -304,7 +309,7 @@ def conv2d_maxpool(x, xshape, bits, w, m, kh, kw, stride=(1, 1), pad=(0, 0), epi
     n, ho, wo, c, obits = _conv_shape(xshape, bits, m, kh, kw, stride, pad, kind)
     yshape = (n, ho // 2, wo // 2, c, obits)
     y = _new_out(yshape, out, x)
-    _call("qnn_conv2d_maxpool", _tensor_bytes(*xshape, bits), x.data_ptr(), m, w.data_ptr(),
+    _call("qnn_conv2d_maxpool", _tensor_bytes(*xshape, bits), x.data_ptr(), m, _addr(w),
           _geom_bytes(kh, kw, stride, pad), _epi_bytes(kind, bias, mult, shift, thresh, clip), 2, 2,
           _tensor_bytes(*yshape), y.data_ptr(), _stream_int(stream))
     return y
@@ -317,7 +322,7 @@ def linear(x, xshape, bits, w, m, epi="raw32", bias=None, mult=None, shift=None,
     obits = {EPI_REQUANT: bits, EPI_THRESH1: 1, EPI_RAW32: 32}[kind]
     yshape = (xshape[0], 1, 1, m, obits)
     y = _new_out(yshape, out, x)
-    _call("qnn_linear", _tensor_bytes(*xshape, bits), x.data_ptr(), m, w.data_ptr(),
+    _call("qnn_linear", _tensor_bytes(*xshape, bits), x.data_ptr(), m, _addr(w),
           _epi_bytes(kind, bias, mult, shift, thresh, clip), _tensor_bytes(*yshape), y.data_ptr(),
           _stream_int(stream))
     return y

@@ -393,3 +393,30 @@ def test_binding_shapes_and_descriptors_agree_with_the_library(q):
         assert qnn._tensor_bytes(*v) == bytes(qnn.Tensor(*v))
     assert qnn._geom_bytes(1, 2, (3, 4), (5, 6)) == bytes(qnn.ConvGeom(1, 2, 3, 4, 5, 6))
     assert qnn._epi_bytes(2, None, None, None, None, (-3, 1 << 32)) == bytes(qnn.Epi(2, None, None, None, None, -3, 1 << 32))
+
+
+class HostStream:
+    """The null stream, without a device."""
+    cuda_stream = 0
+
+
+def binding_status(q, f, *a, **k):
+    try:
+        f(*a, stream=HostStream(), **k)
+    except q.QnnError as e:
+        return e.status
+    return 0
+
+
+def test_binding_passes_a_missing_weight_tensor_on(q):
+    """A weight tensor of None is NULL: the library accepts it with an empty
+    batch and refuses it otherwise."""
+    import torch
+    x = torch.zeros(1024, dtype=torch.uint8)
+    for n, want in ((0, 0), (1, 1)):
+        assert binding_status(q, q.conv2d, x, (n, 4, 4, 4), 8, None, 8, 3, 3, (1, 1), (1, 1), "raw32") == want
+        assert binding_status(q, q.conv2d, x, (n, 4, 4, 4), 8, None, 8, 3, 3, (1, 1), (1, 1), "raw32",
+                              tile=(32, 1, 1, 4)) == want
+        assert binding_status(q, q.conv2d_maxpool, x, (n, 4, 4, 8), 4, None, 8, 3, 3, (1, 1), (1, 1), "stair",
+                              thresh=x) == want
+        assert binding_status(q, q.linear, x, (n, 4, 4, 4), 8, None, 8) == want
