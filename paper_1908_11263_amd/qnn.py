@@ -228,6 +228,12 @@ def out_shape(xshape, bits, m, kh, kw, stride=(1, 1), pad=(0, 0), epi="requant")
     return (y.n, y.h, y.w, y.c, y.bits)
 
 
+# output bits of each epilogue and bit-width that go together
+_OUT_BITS = {(kind, bits): {EPI_REQUANT: bits, EPI_STAIR: bits, EPI_THRESH1: 1, EPI_RAW32: 32}[kind]
+             for kind, widths in ((EPI_REQUANT, (8, 4, 2)), (EPI_STAIR, (4, 2)), (EPI_THRESH1, (1,)),
+                                  (EPI_RAW32, (8, 4, 2, 1))) for bits in widths}
+
+
 def _conv_shape(xshape, bits, m, kh, kw, stride, pad, kind):
     """out_shape, worked out here for every layer the library accepts; the
     others go to the library, which refuses them."""
@@ -235,10 +241,10 @@ def _conv_shape(xshape, bits, m, kh, kw, stride, pad, kind):
     if kh >= 1 and kw >= 1 and stride[0] >= 1 and stride[1] >= 1 and pad[0] >= 0 and pad[1] >= 0:
         ho = (h + 2 * pad[0] - kh) // stride[0] + 1
         wo = (w + 2 * pad[1] - kw) // stride[1] + 1
-        if ho >= 1 and wo >= 1 and n >= 0 and h >= 1 and w >= 1 and c >= 1 and m >= 1:
-            obits = bits if kind == EPI_REQUANT or kind == EPI_STAIR else (1 if kind == EPI_THRESH1 else 32)
+        obits = _OUT_BITS.get((kind, bits))
+        if ho >= 1 and wo >= 1 and n >= 0 and h >= 1 and w >= 1 and c >= 1 and m >= 1 and obits is not None:
             # (sizes near the library's limits are the library's to judge)
-            if bits in (8, 4, 2, 1) and n * h * w * c < 1 << 40 and n * ho * wo * m < 1 << 40:
+            if n * h * w * c < 1 << 40 and n * ho * wo * m < 1 << 40:
                 return (n, ho, wo, m, obits)
     return out_shape(xshape, bits, m, kh, kw, stride, pad, kind)
 

@@ -383,12 +383,10 @@ def test_binding_shapes_and_descriptors_agree_with_the_library(q):
             xs = (xs[0], 1 << 20, 1 << 14, max(1, xs[3]))
         kh, kw, m = r.randint(lo, 6), r.randint(lo, 6), r.randint(lo, 40)
         stride, pad = (r.randint(lo, 3), r.randint(lo, 3)), (r.randint(-1, 3), r.randint(0, 3))
-        bits, kind = r.choice([8, 4, 2, 1, 1, 3]), r.choice([0, 1, 2, 3])
+        bits, kind = r.choice([8, 4, 2, 1, 1, 3]), r.choice([0, 1, 2, 3, -1, 7])
         want = shape_or_status(qnn.out_shape, xs, bits, m, kh, kw, stride, pad, kind)
         got = shape_or_status(qnn._conv_shape, xs, bits, m, kh, kw, stride, pad, kind)
-        # a bit-width and epilogue that do not go together are left to the call itself
-        if want != 2:
-            assert got == want, (xs, bits, m, kh, kw, stride, pad, kind)
+        assert got == want, (xs, bits, m, kh, kw, stride, pad, kind)
     for v in ((1, 2, 3, 4, 8), (1 << 33, 2, 3, 4, 8), (-1, 1 << 31, 0, 4, 1)):
         assert qnn._tensor_bytes(*v) == bytes(qnn.Tensor(*v))
     assert qnn._geom_bytes(1, 2, (3, 4), (5, 6)) == bytes(qnn.ConvGeom(1, 2, 3, 4, 5, 6))
@@ -420,3 +418,20 @@ def test_binding_passes_a_missing_weight_tensor_on(q):
         assert binding_status(q, q.conv2d_maxpool, x, (n, 4, 4, 8), 4, None, 8, 3, 3, (1, 1), (1, 1), "stair",
                               thresh=x) == want
         assert binding_status(q, q.linear, x, (n, 4, 4, 4), 8, None, 8) == want
+
+
+def test_binding_refuses_before_the_output_is_allocated(q):
+    """A bit-width and an epilogue that do not go together: refused by the
+    shape query, with no output buffer asked for."""
+    class NoBuffer:
+        @property
+        def device(self):
+            raise AssertionError("an output buffer was asked for")
+        dtype = new_empty = device
+
+    for bits, kind, want in ((1, "requant", 2), (8, "stair", 2), (1, "stair", 2), (8, "thresh1", 2), (2, "thresh1", 2),
+                             (8, 7, 4), (1, -1, 4)):
+        for f in (q.conv2d, q.conv2d_maxpool):
+            with pytest.raises(q.QnnError, match="qnn_conv2d_out_shape") as e:
+                f(NoBuffer(), (1, 4, 4, 32), bits, NoBuffer(), 8, 3, 3, (1, 1), (1, 1), kind)
+            assert e.value.status == want
