@@ -143,11 +143,6 @@ def _ptr(t):
     return None if t is None else ctypes.c_void_p(t.data_ptr())
 
 
-def _addr(t):
-    """A tensor's address; None (NULL, the library's to accept or refuse) for None."""
-    return None if t is None else t.data_ptr()
-
-
 def _call(name, *args):
     f = _raw.get(name)
     if f is None:
@@ -177,22 +172,16 @@ def _stream_int(stream):
 
 
 _pack5 = struct.Struct("@5i").pack
-_pack6 = struct.Struct("@6i").pack
+_layer = struct.Struct("@13i")  # x's descriptor, the geometry's, m, the epilogue
+_pack_layer, _unpack_layer = _layer.pack, _layer.unpack
 _pack_epi = struct.Struct("@i4x4P2i").pack
 
 
-def _tensor_bytes(n, h, w, c, bits):
+def _tensor_bytes(*v):
     try:
-        return _pack5(n, h, w, c, bits)
+        return _pack5(*v)
     except struct.error:  # a value past 32 bits: as the structure takes it
-        return bytes(Tensor(n, h, w, c, bits))
-
-
-def _geom_bytes(kh, kw, stride, pad):
-    try:
-        return _pack6(kh, kw, stride[0], stride[1], pad[0], pad[1])
-    except struct.error:
-        return bytes(ConvGeom(kh, kw, stride[0], stride[1], pad[0], pad[1]))
+        return bytes(Tensor(*v))
 
 
 def _epi_bytes(kind, bias, mult, shift, thresh, clip):
@@ -234,19 +223,27 @@ _OUT_BITS = {(kind, bits): {EPI_REQUANT: bits, EPI_STAIR: bits, EPI_THRESH1: 1, 
                                   (EPI_RAW32, (8, 4, 2, 1))) for bits in widths}
 
 
-def _conv_shape(xshape, bits, m, kh, kw, stride, pad, kind):
-    """out_shape, worked out here for every layer the library accepts; the
-    others go to the library, which refuses them."""
-    n, h, w, c = xshape
-    if kh >= 1 and kw >= 1 and stride[0] >= 1 and stride[1] >= 1 and pad[0] >= 0 and pad[1] >= 0:
-        ho = (h + 2 * pad[0] - kh) // stride[0] + 1
-        wo = (w + 2 * pad[1] - kw) // stride[1] + 1
-        obits = _OUT_BITS.get((kind, bits))
-        if ho >= 1 and wo >= 1 and n >= 0 and h >= 1 and w >= 1 and c >= 1 and m >= 1 and obits is not None:
-            # (sizes near the library's limits are the library's to judge)
-            if n * h * w * c < 1 << 40 and n * ho * wo * m < 1 << 40:
-                return (n, ho, wo, m, obits)
-    return out_shape(xshape, bits, m, kh, kw, stride, pad, kind)
+def _conv_layer(xshape, bits, m, kh, kw, stride, pad, kind):
+    """(output shape, x's descriptor, geometry's descriptor) of a convolution.
+    The shape is worked out here for every layer that the library accepts; the
+    others, and arguments that are no 13 integers, take the structures and the
+    library's shape query, which accept or refuse them."""
+    try:
+        if len(stride) != 2 or len(pad) != 2:
+            raise TypeError
+        d = _pack_layer(*xshape, bits, kh, kw, *stride, *pad, m, kind)
+    except (struct.error, TypeError):
+        yshape = out_shape(xshape, bits, m, kh, kw, stride, pad, kind)
+        return yshape, bytes(Tensor(*xshape, bits)), bytes(ConvGeom(kh, kw, stride[0], stride[1], pad[0], pad[1]))
+    n, h, w, c, bits, kh, kw, sh, sw, ph, pw, m, kind = _unpack_layer(d)
+    obits = _OUT_BITS.get((kind, bits))
+    if obits and kh > 0 and kw > 0 and sh > 0 and sw > 0 and ph >= 0 and pw >= 0 and n >= 0 and h > 0 and w > 0:
+        ho = (h + 2 * ph - kh) // sh + 1
+        wo = (w + 2 * pw - kw) // sw + 1
+        # (sizes near the library's limits are the library's to judge)
+        if (ho > 0 and wo > 0 and c > 0 and m > 0 and n * h * w * c < 1 << 40 and n * ho * wo * m < 1 << 40):
+            return (n, ho, wo, m, obits), d, d[20:]
+    return out_shape((n, h, w, c), bits, m, kh, kw, (sh, sw), (ph, pw), kind), d, d[20:]
 
 
 def _new_out(shape, out, x):
@@ -293,16 +290,15 @@ def conv2d(x, xshape, bits, w, m, kh, kw, stride=(1, 1), pad=(0, 0), epi="requan
     tile = (kernel, tile_m, tile_n, waves) picks the tile shape
     (qnn_conv2d_tiled) instead of the library."""
     kind = _EPI_NAMES[epi] if isinstance(epi, str) else epi
-    yshape = _conv_shape(xshape, bits, m, kh, kw, stride, pad, kind)
+    yshape, xd, g = _conv_layer(xshape, bits, m, kh, kw, stride, pad, kind)
     y = _new_out(yshape, out, x)
-    xd = _tensor_bytes(*xshape, bits)
     yd = _tensor_bytes(*yshape)
-    g = _geom_bytes(kh, kw, stride, pad)
     e = _epi_bytes(kind, bias, mult, shift, thresh, clip)
+    wp = None if w is None else w.data_ptr()  # (None: NULL, the library's to accept or refuse)
     if tile is None:
-        _call("qnn_conv2d", xd, x.data_ptr(), m, _addr(w), g, e, yd, y.data_ptr(), _stream_int(stream))
+        _call("qnn_conv2d", xd, x.data_ptr(), m, wp, g, e, yd, y.data_ptr(), _stream_int(stream))
     else:
-        _call("qnn_conv2d_tiled", xd, x.data_ptr(), m, _addr(w), g, e, bytes(Tile(*tile)), yd, y.data_ptr(),
+        _call("qnn_conv2d_tiled", xd, x.data_ptr(), m, wp, g, e, bytes(Tile(*tile)), yd, y.data_ptr(),
               _stream_int(stream))
     return y
 
@@ -312,12 +308,13 @@ def conv2d_maxpool(x, xshape, bits, w, m, kh, kw, stride=(1, 1), pad=(0, 0), epi
     """Convolution fused with 2x2 / stride-2 max-pooling (qnn_conv2d_maxpool).
     Returns uint8 [N, floor(Ho/2), floor(Wo/2), out bytes] codes."""
     kind = _EPI_NAMES[epi] if isinstance(epi, str) else epi
-    n, ho, wo, c, obits = _conv_shape(xshape, bits, m, kh, kw, stride, pad, kind)
+    (n, ho, wo, c, obits), xd, g = _conv_layer(xshape, bits, m, kh, kw, stride, pad, kind)
     yshape = (n, ho // 2, wo // 2, c, obits)
     y = _new_out(yshape, out, x)
-    _call("qnn_conv2d_maxpool", _tensor_bytes(*xshape, bits), x.data_ptr(), m, _addr(w),
-          _geom_bytes(kh, kw, stride, pad), _epi_bytes(kind, bias, mult, shift, thresh, clip), 2, 2,
-          _tensor_bytes(*yshape), y.data_ptr(), _stream_int(stream))
+    wp = None if w is None else w.data_ptr()
+    _call("qnn_conv2d_maxpool", xd, x.data_ptr(), m, wp, g,
+          _epi_bytes(kind, bias, mult, shift, thresh, clip), 2, 2, _tensor_bytes(*yshape), y.data_ptr(),
+          _stream_int(stream))
     return y
 
 
@@ -328,7 +325,8 @@ def linear(x, xshape, bits, w, m, epi="raw32", bias=None, mult=None, shift=None,
     obits = {EPI_REQUANT: bits, EPI_THRESH1: 1, EPI_RAW32: 32}[kind]
     yshape = (xshape[0], 1, 1, m, obits)
     y = _new_out(yshape, out, x)
-    _call("qnn_linear", _tensor_bytes(*xshape, bits), x.data_ptr(), m, _addr(w),
+    wp = None if w is None else w.data_ptr()
+    _call("qnn_linear", _tensor_bytes(*xshape, bits), x.data_ptr(), m, wp,
           _epi_bytes(kind, bias, mult, shift, thresh, clip), _tensor_bytes(*yshape), y.data_ptr(),
           _stream_int(stream))
     return y

@@ -385,11 +385,13 @@ def test_binding_shapes_and_descriptors_agree_with_the_library(q):
         stride, pad = (r.randint(lo, 3), r.randint(lo, 3)), (r.randint(-1, 3), r.randint(0, 3))
         bits, kind = r.choice([8, 4, 2, 1, 1, 3]), r.choice([0, 1, 2, 3, -1, 7])
         want = shape_or_status(qnn.out_shape, xs, bits, m, kh, kw, stride, pad, kind)
-        got = shape_or_status(qnn._conv_shape, xs, bits, m, kh, kw, stride, pad, kind)
+        got = shape_or_status(lambda *a: qnn._conv_layer(*a)[0], xs, bits, m, kh, kw, stride, pad, kind)
         assert got == want, (xs, bits, m, kh, kw, stride, pad, kind)
     for v in ((1, 2, 3, 4, 8), (1 << 33, 2, 3, 4, 8), (-1, 1 << 31, 0, 4, 1)):
         assert qnn._tensor_bytes(*v) == bytes(qnn.Tensor(*v))
-    assert qnn._geom_bytes(1, 2, (3, 4), (5, 6)) == bytes(qnn.ConvGeom(1, 2, 3, 4, 5, 6))
+    xs = (3, 9, 8, 7)
+    _, xd, g = qnn._conv_layer(xs, 8, 5, 1, 2, (3, 4), (5, 6), 0)  # (the library reads the first fields)
+    assert xd.startswith(bytes(qnn.Tensor(*xs, 8))) and g.startswith(bytes(qnn.ConvGeom(1, 2, 3, 4, 5, 6)))
     assert qnn._epi_bytes(2, None, None, None, None, (-3, 1 << 32)) == bytes(qnn.Epi(2, None, None, None, None, -3, 1 << 32))
 
 
@@ -435,3 +437,13 @@ def test_binding_refuses_before_the_output_is_allocated(q):
             with pytest.raises(q.QnnError, match="qnn_conv2d_out_shape") as e:
                 f(NoBuffer(), (1, 4, 4, 32), bits, NoBuffer(), 8, 3, 3, (1, 1), (1, 1), kind)
             assert e.value.status == want
+
+
+def test_binding_refuses_strides_and_pads_of_another_length(q):
+    import torch
+    x = torch.zeros(1024, dtype=torch.uint8)
+    for stride, pad in (((1, 1, 1), (1, 1)), ((1, 1), (1, 1, 1)), ((1, 1, 1, 1), (1, 1)), ((1,), (1, 1, 1)),
+                        ((1.0, 1.0), (1, 1)), (1, (1, 1))):
+        for f in (q.conv2d, q.conv2d_maxpool):
+            with pytest.raises((TypeError, IndexError)):
+                f(x, (1, 4, 4, 32), 8, x, 8, 3, 3, stride, pad, "requant", mult=x, shift=x, stream=HostStream())
