@@ -562,6 +562,14 @@ constexpr StreamTile kStreamTiles[] = {QNN_STREAM_VARIANTS(QNN_STREAM_TILE)};
 #undef QNN_STREAM_TILE
 #undef QNN_STREAM_HAS
 
+// Workgroups of the streaming kernel that a compute unit holds.
+int64_t stream_resident(const StreamArgs &a, const StreamTile &T)
+{
+    const int64_t regs = T.wm * T.wn >= 6 ? 2 : (T.wm * T.wn >= 4 ? 3 : 4);
+    const int64_t lds = kLdsBytes / a.lds_bytes;
+    return lds < regs ? lds : regs;
+}
+
 bool plan_stream(StreamArgs &best, int &variant, const qnn_tensor *x, int32_t m, const qnn_conv_geom *g,
                  const qnn_epi *e, int32_t ho, int32_t wo, bool pool)
 {
@@ -702,10 +710,7 @@ bool plan_stream(StreamArgs &best, int &variant, const qnn_tensor *x, int32_t m,
         // of its MFMAs, its LDS traffic (128 B per clock) and its loads (about
         // 32 B per clock and compute unit); a lone workgroup also waits out
         // the loads' latency, which others on its compute unit cover
-        const int regs_wg = T.wm * T.wn >= 6 ? 2 : (T.wm * T.wn >= 4 ? 3 : 4);
-        int64_t occ = kLdsBytes / c.lds_bytes;
-        if (occ > regs_wg)
-            occ = regs_wg;
+        const int64_t occ = stream_resident(c, T);
         const int64_t units = mtiles * ptiles;
         const int64_t conc = (units + kPlanCus - 1) / kPlanCus < occ ? (units + kPlanCus - 1) / kPlanCus : occ;
         const double xshare = (double)a.nblk / (double)steps;  // blocks per step
@@ -729,6 +734,88 @@ bool plan_stream(StreamArgs &best, int &variant, const qnn_tensor *x, int32_t m,
         }
     }
     return variant >= 0;
+}
+
+// Where the streaming kernel can lose to the tile kernels: a compute unit has
+// one workgroup (a small grid, or input tiles of wide rows that fill the local
+// memory), so nothing covers the latency of its steps, or an input tile, which
+// is whole rows, stages four and more pixels per one it needs.  Elsewhere it
+// was the slower one, by more than 7%, in 1% of 6981 random layers.
+bool stream_weak(const StreamArgs &a, int variant)
+{
+    const StreamTile &T = kStreamTiles[variant];
+    const int PT = 32 * T.wn * (4 / T.wch);
+    return (int64_t)a.ptiles * a.mtiles <= kPlanCus || stream_resident(a, T) <= 1 ||
+           (!a.pw1 && a.nslots >= (int64_t)4 * PT * a.ssh * a.ssw);
+}
+
+// Predicted microseconds of both kernels, for layers where stream_weak holds.
+// The terms are the parts of each kernel's work that take time where little
+// runs at once; their coefficients are least-squares fits to the times of
+// 31,753 random layers (8, 4 and 2 bits, 1 to 1024 columns, 1x1 to 7x7
+// filters, 1 to 256 images; graph replays of each kernel, near ties weighted
+// most).  Each prediction is within about 13% (one standard deviation).  The
+// sampled layers took 3.1% longer than the faster of the two kernels with the
+// streaming kernel always, 0.4% longer with this choice; slower than the tile
+// kernels by more than 7% were 9.9% of them, now 1.2%.  INT-4 22x64x1024x16,
+// 3x3, 16 channels, pooled: 161.8 -> 44.6 us; INT-4 3x11x8x544, 3x3, 56
+// channels: 32.7 -> 14.1; INT-8 8x16x640x8, 7x7, 16 channels: 37.1 -> 14.2.
+double stream_us(const StreamArgs &a, int variant)
+{
+    const StreamTile &T = kStreamTiles[variant];
+    const int64_t units = (int64_t)a.ptiles * a.mtiles, per_cu = (units + kPlanCus - 1) / kPlanCus;
+    const int64_t occ = stream_resident(a, T), conc = per_cu < occ ? per_cu : occ;
+    const double rounds = (double)((units + kPlanCus * conc - 1) / (kPlanCus * conc));
+    const int nblk = a.lg == 2 ? a.nblk : 1, spb = a.lg == 2 ? a.taps : a.nlast;
+    const double blocks = a.pw1 ? 0 : nblk;
+    // steps between barriers: one-tap filters' take one slice, the others'
+    // run in pairs of one slice or one by one with two
+    const double steps = a.pw1 ? nblk : (double)nblk * ((spb + 1) / 2) * (T.g == 2 ? 1 : 2);
+    double us = 3.5 + steps * (a.pw1 ? 0.24 : (T.g == 2 ? 0.30 : 0.17));
+    if (a.tail && !a.pw1)
+        us += steps * 0.10;
+    if (a.dw)  // word by word
+        us += steps * 0.046 + blocks * a.nbatch * 0.14;
+    us += (double)conc * nblk * spb * T.wm * T.wn * 0.064;             // matrix instructions
+    us += blocks * 0.43 + blocks * ((a.nbatch - 1) / 2) * 0.69;        // input batches past the two in flight wait
+    us += a.pw1 ? 0.0 : a.nslots * 0.0007;                             // pixel offsets
+    us += a.epi == EPI_STAIR ? 0.76 : 0.0;
+    return 0.7 + rounds * us;
+}
+
+// The same of a tile kernel's plan: tiles of MT channels and PT outputs.
+double tile_us(const ConvArgs &a, int bits, bool use32, int MT, int PT, int nw)
+{
+    // us per 1000 filter words staged singly (filter rows that are no whole
+    // 16-byte quads), the same again for walks along filter rows, 8-bit filter
+    // quads, filter bytes in LDS, input words, input quads; per ten K steps and
+    // ten matrix instructions of a wave; per 1000 outputs of a tile, the same
+    // again at 8 bits and for staircases
+    struct Cost {
+        double base, fw, frow, fq8, flds, xw, xq, step, mfma, out, out8, stair;
+    };
+    static const Cost k16 = {5.3, 0.76, 0.053, 0.95, 0.0, 0.80, 1.1, 0.92, 0.13, 0.12, 0.48, 0.28};
+    static const Cost k32 = {4.4, 0.096, 0.19, 0.94, 0.019, 0.95, 1.1, 0.27, 0.084, 0.21, 0.24, 0.12};
+    const Cost &k = use32 ? k32 : k16;
+    const int64_t mtiles = (a.m + MT - 1) / MT;
+    const int64_t per_cu = a.lds_bytes * 2 <= kLdsBytes && nw == 4 ? 2 : 1;
+    const int64_t gx = kPlanCus * per_cu < a.ntiles ? kPlanCus * per_cu : a.ntiles;
+    const int64_t groups = gx * mtiles, most = (groups + kPlanCus - 1) / kPlanCus;
+    const int64_t conc = most < per_cu ? most : per_cu;
+    const double rounds = (double)((groups + kPlanCus * conc - 1) / (kPlanCus * conc));
+    const double tiles = (double)((a.ntiles + gx - 1) / gx);
+    const double K = (double)a.wrow * 8 / bits;
+    const bool eight = bits == 8, fast_w = !a.row_mode && a.wrow % 16 == 0, fast_x = a.pb % 16 == 0;
+    double fill = MT * (double)a.kp * k.flds;
+    if (!fast_w)
+        fill += MT * K / 4 * (k.fw + (a.row_mode ? k.frow : 0.0));
+    else if (eight)
+        fill += MT * (double)a.wrow / 16 * k.fq8;
+    const double px = (double)a.ti * a.hh * a.hwd * a.pb;
+    const double mf = use32 ? (double)(MT / 32) * (PT / (32 * nw)) * a.ksteps * 2 : (double)(MT / 16) * (PT / 64) * a.ksteps;
+    const double tile = (fast_x ? px / 16 * k.xq : px / 4 * k.xw) + 100 * (a.ksteps * k.step + conc * mf * k.mfma) +
+                        (double)MT * PT * (k.out + (eight ? k.out8 : 0.0) + (a.epi == EPI_STAIR ? k.stair : 0.0));
+    return k.base + rounds * (fill + tiles * tile) * 0.001;
 }
 
 // Launches the streaming kernel on a planned layer.
@@ -967,16 +1054,21 @@ qnn_status run_conv(const qnn_tensor *x, const void *x_dev, int32_t m, const voi
     st = device_info(&cus);
     if (st != QNN_OK)
         return st;
-    // every layer that the tile kernels take goes to the streaming kernel,
-    // unless the caller forces a tile, except small narrow ones: with at most
-    // 24 output channels and fewer than a quarter of the device's workgroups
-    // the 16-channel tiles of the 16x16 kernel give more of them (7 images of
-    // 59x13x96 INT-4 codes to 23 channels: 7.5 against 10.8 us)
+    // the layers that the tile kernels take go to the streaming kernel, unless
+    // the caller forces a tile, except
+    // - small narrow ones: with at most 24 output channels and fewer than a
+    //   quarter of the device's workgroups the 16-channel tiles of the 16x16
+    //   kernel give more of them (7 images of 59x13x96 INT-4 codes to 23
+    //   channels: 7.5 against 10.8 us);
+    // - where it is weak and the tile kernels' predicted time is the lower one
     if (!force) {
         StreamArgs sa;
         int variant;
         if (plan_stream(sa, variant, x, m, g, e, ho, wo, pool) &&
-            !(!pool && m <= 24 && (int64_t)sa.ptiles * sa.mtiles < cus / 4))
+            !(!pool && m <= 24 && (int64_t)sa.ptiles * sa.mtiles < cus / 4) &&
+            !(stream_weak(sa, variant) &&
+              tile_us(a, x->bits, use32, use32 ? 32 * wm : 16 * mr, use32 ? 32 * wn * nw : 64 * nc, nw) * 1.02 <
+                  stream_us(sa, variant)))
             return run_stream(sa, variant, x->bits, x_dev, w_dev, e, y_dev, ypb, s);
     }
     if (use32 && nw == 8 && a.ntiles > cus && !f4) {

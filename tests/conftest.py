@@ -17,3 +17,9 @@ def orc():
     import oracle
     oracle.build()
     return oracle
+
+
+@pytest.fixture(scope="session")
+def route_lib(tmp_path_factory):
+    import routes
+    return routes.build(tmp_path_factory.mktemp("routes"))
