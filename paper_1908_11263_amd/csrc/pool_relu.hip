@@ -135,8 +135,9 @@ __device__ __forceinline__ uint32_t relu_word(uint32_t v)
     return v & ~((neg << 8) - neg);
 }
 
-// 16 bytes per lane; the last lane takes what is left, byte by byte.  The
-// input is read once: non-temporal loads leave the memory-side cache to the
+// 16 bytes per lane, and a lane per byte of what is left (one lane for all of
+// it is a chain of up to 15 loads and stores: 1.1 us of 3.3 us at 4207 bytes).
+// The input is read once: non-temporal loads leave the memory-side cache to the
 // output, which the next layer reads (with the pooling that follows 58.8 ->
 // 51.7 us, side by side).
 __global__ void __launch_bounds__(256) relu_s8_kernel(const uint8_t *x, uint8_t *y, size_t count)
@@ -147,17 +148,16 @@ __global__ void __launch_bounds__(256) relu_s8_kernel(const uint8_t *x, uint8_t 
         typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
         const u32x4 v = __builtin_nontemporal_load((const u32x4 *)x + i);
         ((uint4 *)y)[i] = make_uint4(relu_word(v.x), relu_word(v.y), relu_word(v.z), relu_word(v.w));
-    } else if (i == quads) {
-        for (size_t b = quads * 16; b < count; ++b) {
-            const int8_t v = (int8_t)x[b];
-            y[b] = (uint8_t)(v > 0 ? v : 0);
-        }
+    } else if (i < quads + (count & 15)) {
+        const size_t b = quads * 16 + (i - quads);
+        const int8_t v = (int8_t)x[b];
+        y[b] = (uint8_t)(v > 0 ? v : 0);
     }
 }
 
 hipError_t launch_relu_s8(const uint8_t *x, uint8_t *y, size_t count, hipStream_t s)
 {
-    dim3 grid((unsigned)((count / 16 + 256) / 256));
+    dim3 grid((unsigned)((count / 16 + (count & 15) + 255) / 256));
     hipLaunchKernelGGL(relu_s8_kernel, grid, dim3(256), 0, s, x, y, count);
     return hipGetLastError();
 }
