@@ -139,3 +139,15 @@ def test_relu_remainders(qnn, count):
     want = np.where(x >= 128, 0, x).astype(np.uint8)
     compare(y.cpu().numpy(), want, "relu %d" % count)
     compare(d.cpu().numpy(), want, "relu in place %d" % count)
+
+
+@pytest.mark.parametrize("bits", [8, 4, 2])
+@pytest.mark.parametrize("w", [259, 260])
+def test_maxpool_wide_window_by_words_and_quads(qnn, orc, bits, w):
+    """A window without an instance of its own on either side of 65536 quads."""
+    import torch
+    c = 128 // bits
+    x = np.random.default_rng(w + bits).integers(0, 256, size=(1, 260, w, 16), dtype=np.uint8)
+    got = qnn.maxpool2d(dev(x), (1, 260, w, c), bits, 5, 5, 1, 1)
+    torch.cuda.synchronize()
+    compare(got.cpu().numpy(), orc.maxpool2d(x, (1, 260, w, c), bits, 5, 5, 1, 1), "maxpool 5x5 %d-bit w=%d" % (bits, w))
