@@ -1247,23 +1247,9 @@ hipError_t launch_img_grid(K kernel, const ImgArgs &a, int flds, int cus, hipStr
             attr_set = true;
         }
     }
-    // the query takes a good part of a launch's host time: its answers are
-    // kept per thread, for the kernel and local memory they were given for
-    // (every device the library runs on is a gfx950)
-    struct Asked {
-        const void *kernel;
-        size_t lds;
-        int per_cu;
-    };
-    static thread_local Asked known[32];
-    Asked &q = known[(((uintptr_t)kernel >> 4) ^ (lds >> 4)) & 31];
-    if (q.kernel != (const void *)kernel || q.lds != lds) {
-        int n = 0;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, kernel, 256, lds) != hipSuccess || n < 1)
-            n = 1;
-        q = {(const void *)kernel, lds, n};
-    }
-    const int per_cu = q.per_cu;
+    const int per_cu = resident_workgroups((const void *)kernel, lds, [&](int *n) {
+        return hipOccupancyMaxActiveBlocksPerMultiprocessor(n, kernel, 256, lds);
+    });
     const int gy = (a.m + 31) / 32;
     int64_t gx = ((int64_t)cus * per_cu + gy - 1) / gy;
     if (gx > a.ngroups)

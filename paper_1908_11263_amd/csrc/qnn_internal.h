@@ -29,6 +29,33 @@ __device__ __forceinline__ uint32_t fdiv(uint32_t n, const FastDiv &f)
     return (__umulhi(n, f.mul) + n) >> f.shr;
 }
 
+// Workgroups of `kernel` with `lds` bytes of local memory that a compute unit
+// holds, by query(&n).  The query takes a good part of a launch's host time:
+// its answers are kept per thread, for the kernel and local memory they were
+// given for (every device the library runs on is a gfx950).  A failed query
+// counts as one workgroup for this call, is asked again at the next, and
+// leaves no error behind for the launch to report.
+template <typename Query>
+int resident_workgroups(const void *kernel, size_t lds, Query query)
+{
+    struct Asked {
+        const void *kernel;
+        size_t lds;
+        int n;
+    };
+    static thread_local Asked known[32];
+    Asked &q = known[(((uintptr_t)kernel >> 4) ^ (lds >> 4)) & 31];
+    if (q.kernel != kernel || q.lds != lds) {
+        int n = 0;
+        if (query(&n) != hipSuccess || n < 1) {
+            (void)hipGetLastError();
+            return 1;
+        }
+        q = {kernel, lds, n};
+    }
+    return q.n;
+}
+
 enum { EPI_REQUANT = 0, EPI_THRESH1 = 1, EPI_RAW32 = 2, EPI_STAIR = 3 };
 
 // Arguments of the int8-MFMA implicit-GEMM convolution (8/4/2-bit inputs).

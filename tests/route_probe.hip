@@ -71,6 +71,21 @@ hipError_t hipGetDeviceProperties(hipDeviceProp_t *p, int)
     return hipSuccess;
 }
 
+hipError_t hipGetLastError(void)
+{
+    return hipSuccess;
+}
+
+// resident_workgroups of kernel k with a query that answers `status` and n; asked: queries made so far
+int32_t probe_resident(int32_t k, int32_t lds, int32_t status, int32_t n, int32_t *asked)
+{
+    return resident_workgroups((const void *)(intptr_t)(0x1000 * k), (size_t)lds, [&](int *out) {
+        ++*asked;
+        *out = n;
+        return (hipError_t)status;
+    });
+}
+
 // status of a call of run_conv on pointers that nothing reads; *r: what it launched
 int32_t probe_conv(const qnn_tensor *x, int32_t m, const qnn_conv_geom *g, int32_t epi, const qnn_tensor *y, int32_t pool,
                    Route *r)

@@ -30,6 +30,8 @@ def build(folder):
     P, I = ctypes.c_void_p, ctypes.c_int32
     L.probe_conv.restype = I
     L.probe_conv.argtypes = [P, I, P, I, P, I, P]
+    L.probe_resident.restype = I
+    L.probe_resident.argtypes = [I, I, I, I, P]
     return L
 
 

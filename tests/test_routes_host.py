@@ -1,5 +1,7 @@
 """Which kernel the library picks for a layer, worked out on the CPU
 (routes.py: the library's own dispatch with its launches recorded)."""
+import ctypes
+
 import pytest
 
 import routes
@@ -43,3 +45,18 @@ def test_the_faster_kernel_is_picked(route_lib, layer, kernel, tile_us, stream_u
     r = routes.route(route_lib, *layer)
     assert r.status == 0 and r.kernel == kernel
     assert (r.kernel == "stream") == (stream_us < tile_us)
+
+
+def test_a_failed_occupancy_query_is_not_kept(route_lib):
+    """The image kernels' resident workgroups: an answer is kept for its kernel
+    and local memory, a failure (or no workgroup) is asked again."""
+    asked = ctypes.c_int32(0)
+
+    def ask(kernel, lds, status, n):
+        return route_lib.probe_resident(kernel, lds, status, n, ctypes.byref(asked))
+
+    assert ask(1, 4096, 1, 0) == 1 and asked.value == 1     # failed
+    assert ask(1, 4096, 0, 0) == 1 and asked.value == 2     # no workgroup
+    assert ask(1, 4096, 0, 3) == 3 and asked.value == 3
+    assert ask(1, 4096, 0, 7) == 3 and asked.value == 3     # kept
+    assert ask(1, 8192, 0, 2) == 2 and ask(2, 4096, 0, 5) == 5 and asked.value == 5
