@@ -1138,10 +1138,10 @@ hipError_t launch_conv_stream_bits(const StreamArgs &a, int variant, hipStream_t
 #define QNN_STREAM_M(V_, WM_, WN_, WCH_, G_, MODE_, LG_, TAIL_, PW_)                                  \
     if (variant == V_ && mode == MODE_ && a.lg == LG_ && a.pw1 == PW_) {                              \
         auto *k = conv_stream_kernel<BITS, WM_, WN_, WCH_, G_, MODE_, LG_, TAIL_, PW_, XP>;               \
-        if (a.lds_bytes > 64 * 1024 &&                                                                \
-            hipFuncSetAttribute((const void *)k, hipFuncAttributeMaxDynamicSharedMemorySize,          \
-                                160 * 1024) != hipSuccess)                                            \
-            (void)hipGetLastError();                                                                  \
+        if (a.lds_bytes > 64 * 1024) {                                                                \
+            static std::atomic<uint64_t> devices{0};                                                  \
+            allow_large_lds((const void *)k, devices);                                                \
+        }                                                                                             \
         hipLaunchKernelGGL(k, grid, dim3(256), a.lds_bytes, s, a);                                    \
         return hipGetLastError();                                                                     \
     }

@@ -1,6 +1,7 @@
 // Internal declarations shared by the host dispatcher and the gfx950 kernels.
 #pragma once
 
+#include <atomic>
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -27,6 +28,23 @@ inline FastDiv make_fastdiv(uint32_t d)
 __device__ __forceinline__ uint32_t fdiv(uint32_t n, const FastDiv &f)
 {
     return (__umulhi(n, f.mul) + n) >> f.shr;
+}
+
+// Lets `kernel` have the compute unit's 160 KB of local memory, past the 64 KB
+// that a launch may ask for by default; asked for once per device (bits of
+// `devices`, one such word per kernel instance) because it costs a launch about
+// a tenth of its host time.
+inline void allow_large_lds(const void *kernel, std::atomic<uint64_t> &devices)
+{
+    int dev = 0;
+    const bool known = hipGetDevice(&dev) == hipSuccess && dev >= 0 && dev < 64;
+    const uint64_t bit = known ? (uint64_t)1 << dev : 0;
+    if (devices.load(std::memory_order_relaxed) & bit)
+        return;
+    if (hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024) == hipSuccess)
+        devices.fetch_or(bit, std::memory_order_relaxed);
+    else
+        (void)hipGetLastError();
 }
 
 // Workgroups of `kernel` with `lds` bytes of local memory that a compute unit

@@ -58,10 +58,30 @@ hipError_t launch_relu_s8(const uint8_t *, uint8_t *, size_t, hipStream_t) { ret
 
 extern "C" {
 
+static int g_device, g_attr_calls;
+static hipError_t g_attr_status;
+
 hipError_t hipGetDevice(int *d)
 {
-    *d = 0;
+    *d = g_device;
     return hipSuccess;
+}
+
+hipError_t hipFuncSetAttribute(const void *, hipFuncAttribute, int)
+{
+    ++g_attr_calls;
+    return g_attr_status;
+}
+
+// allow_large_lds on a device whose runtime answers `status`; attribute calls so far
+int32_t probe_large_lds(int32_t device, int32_t status)
+{
+    static std::atomic<uint64_t> devices{0};
+    g_device = device;
+    g_attr_status = (hipError_t)status;
+    allow_large_lds(nullptr, devices);
+    g_device = 0;
+    return g_attr_calls;
 }
 
 hipError_t hipGetDeviceProperties(hipDeviceProp_t *p, int)

@@ -60,3 +60,9 @@ def test_a_failed_occupancy_query_is_not_kept(route_lib):
     assert ask(1, 4096, 0, 3) == 3 and asked.value == 3
     assert ask(1, 4096, 0, 7) == 3 and asked.value == 3     # kept
     assert ask(1, 8192, 0, 2) == 2 and ask(2, 4096, 0, 5) == 5 and asked.value == 5
+
+
+def test_large_local_memory_is_asked_for_once_per_device(route_lib):
+    calls = [route_lib.probe_large_lds(dev, status) for dev, status in
+             ((0, 1), (0, 0), (0, 0), (3, 0), (0, 0), (3, 0), (70, 0), (70, 0))]
+    assert calls == [1, 2, 2, 3, 3, 3, 4, 5]  # (a failure, and a device past the table, are asked for again)
