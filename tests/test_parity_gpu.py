@@ -283,7 +283,8 @@ def test_relu_s8(qnn, orc):
 
 
 def test_int1_register_resident_shapes(qnn, orc):
-    """Filter volumes of 8..128 words take the register-resident XNOR path."""
+    """Filter volumes of 8..128 words (small images: the streaming kernel's;
+    the register-resident XNOR path's layers are in test_parity_routes_gpu.py)."""
     for (c, k, m) in [(256, 1, 40), (64, 2, 32), (256, 3, 64), (128, 4, 33), (512, 2, 70),
                       (1024, 1, 8), (256, 4, 32), (128, 5, 32)]:
         check_layer(orc, make(1, 2, 7, 6, c, m, k, pad=k // 2))
@@ -291,9 +292,9 @@ def test_int1_register_resident_shapes(qnn, orc):
 
 def test_int1_every_register_resident_volume(qnn, orc):
     """Every filter volume the register-resident XNOR kernel is built for
-    (8..128 words in steps of 8), through the quad-wide im2col gather
-    (channel words a multiple of 4) and the word-by-word one, with binary
-    threshold and raw outputs."""
+    (8..128 words in steps of 8), as pixels of whole 16-byte quads and not,
+    with binary threshold and raw outputs (small images: on the streaming
+    kernel)."""
     cases = [(256 * j, 1) for j in range(1, 17)]            # 1x1 filters, 8j words per pixel
     cases += [(64, 2), (192, 2), (64, 4), (320, 2), (64, 6), (96, 4)]  # 2 or 6 words per tap
     for i, (c, k) in enumerate(cases):

@@ -1,11 +1,13 @@
-"""GPU parity of the streaming implicit-GEMM kernel (the library's own pick for
-general layers) against the oracle, byte for byte, at the sizes where its tiles,
-blocks and loads end: partly filled channel and output tiles, tiles that run on
-into the next image, narrow pixels (several taps per step), pixels that end
-inside a 16-byte item or a 64-byte block, several channel blocks, one-tap
-filters, strides, whole-image filters, every epilogue and plan form."""
+"""GPU parity of general layers (most on the streaming implicit-GEMM kernel; the
+small narrow ones at 4 and 2 bits on the 16x16 tiles) against the oracle,
+byte for byte, at the sizes where the streaming kernel's tiles, blocks and
+loads end: partly filled channel and output tiles, tiles that run on into the
+next image, narrow pixels (several taps per step), pixels that end inside a
+16-byte item or a 64-byte block, several channel blocks, one-tap filters,
+strides, whole-image filters, every epilogue and plan form."""
 import pytest
 
+import layers
 import synth
 from gpu_helpers import compare, dev, gpu_conv, oracle_conv
 from test_parity_pool_gpu import gpu_pool, oracle_pool
@@ -85,9 +87,7 @@ def test_tiles_and_strides(qnn, orc, bits):
 def test_packed_input_tiles(qnn, orc, epi):
     """4-bit layers whose input tiles stay packed in local memory because more
     workgroups fit (whole and odd blocks; one-tap filters always do)."""
-    for i, (n, h, w, c, m, k, s) in enumerate([
-            (137, 13, 70, 64, 72, 3, 2), (46, 40, 41, 64, 40, 5, 2), (94, 40, 41, 88, 40, 3, 2),
-            (87, 40, 41, 64, 130, 1, 1), (63, 20, 41, 88, 130, 1, 2), (40, 11, 9, 72, 34, 1, 1)]):
+    for i, (n, h, w, c, m, k, s) in enumerate(layers.PACKED_POOLED if epi == "pool" else layers.PACKED):
         L = layer(4, n, h, w, c, m, k, stride=s, seed=60 + i, epi="requant" if epi == "pool" else epi)
         if epi == "pool":
             compare(gpu_pool(qnn, L), oracle_pool(orc, L), "packed case %d pooled" % i)
@@ -125,6 +125,6 @@ def test_linear_long_reduction(qnn, orc, bits):
 
 def test_wide_binary_rows_take_the_popcount_kernel(qnn, orc):
     """Rows too wide for the streaming kernel's input tile."""
-    for (h, w, c, m, k) in [(3, 1200, 512, 33, 3), (2, 9000, 32, 8, 1), (9, 40, 32, 12, 9)]:
+    for (h, w, c, m, k) in layers.WIDE_BINARY:
         L = layer(1, 1, h, w, c, m, k, seed=w)
         compare(gpu_conv(L), oracle_conv(orc, L), "wide int1 %d" % w)

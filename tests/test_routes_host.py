@@ -1,9 +1,12 @@
 """Which kernel the library picks for a layer, worked out on the CPU
 (routes.py: the library's own dispatch with its launches recorded)."""
 import ctypes
+import math
+import random
 
 import pytest
 
+import layers
 import routes
 
 
@@ -66,3 +69,61 @@ def test_large_local_memory_is_asked_for_once_per_device(route_lib):
     calls = [route_lib.probe_large_lds(dev, status) for dev, status in
              ((0, 1), (0, 0), (0, 0), (3, 0), (0, 0), (3, 0), (70, 0), (70, 0))]
     assert calls == [1, 2, 2, 3, 3, 3, 4, 5]  # (a failure, and a device past the table, are asked for again)
+
+
+def test_stream_layers_take_every_instance_that_is_picked(route_lib):
+    """Every layer of the table takes the instance written beside it, and random
+    layers take none that the table lacks."""
+    table = set()
+    for layer, want in layers.stream_layers():
+        r = routes.route(route_lib, *layer)
+        got = (r.tile, r.lg, r.tail, r.one_tap, r.packed, r.dw, int(r.nblk > 1))
+        assert r.kernel == "stream" and got == want, (layer, r)
+        table.add((layer[0], layer[10], layer[11]) + want[:5])
+    rng = random.Random(17)
+
+    def log_int(lo, hi):
+        return int(round(math.exp(rng.uniform(math.log(lo), math.log(hi)))))
+
+    seen = 0
+    for _ in range(60000):
+        bits = rng.choice([8, 4, 2, 1])
+        pool = bits != 1 and rng.random() < 0.3
+        epi = rng.choice(["thresh1", "raw32"] if bits == 1 else
+                         ["requant"] + ([] if pool else ["raw32"]) + (["stair"] if bits < 8 else []))
+        n, h, w = log_int(1, 3000), log_int(2, 80), log_int(2, 80)
+        c, m = 32 // bits * log_int(1, 64), log_int(1, 300)
+        k, s = rng.choice([1, 1, 2, 3, 3, 5]), rng.choice([1, 1, 2, 3])
+        pad = rng.choice([0, k // 2])
+        if min(h, w) + 2 * pad - k < s:
+            continue
+        r = routes.route(route_lib, bits, n, h, w, c, m, k, k, s, pad, epi, pool)
+        if r.status == 0 and r.kernel == "stream":
+            seen += 1
+            assert (bits, epi, pool, r.tile, r.lg, r.tail, r.one_tap, r.packed) in table
+    assert seen > 20000
+
+
+@pytest.mark.parametrize("layer,words,resident", layers.XNOR)
+def test_xnor_layers_take_the_popcount_kernels(route_lib, layer, words, resident):
+    r = routes.route(route_lib, *layer)
+    assert (r.status, r.kernel, r.tile, r.mode) == (0, "xnor", words, resident)
+
+
+@pytest.mark.parametrize("layer,tile", layers.POOLED_TILES)
+def test_pooled_layers_on_the_tile_kernel(route_lib, layer, tile):
+    r = routes.route(route_lib, *layer)
+    assert (r.status, r.kernel, r.tile, r.mode) == (0, "mfma32", tile, 2)
+
+
+def test_layers_of_the_other_streaming_tests(route_lib):
+    """The layers that tests name by their kernel take it."""
+    for pool in (False, True):
+        for (n, h, w, c, m, k, s) in layers.PACKED_POOLED if pool else layers.PACKED:
+            for epi in ("requant",) if pool else ("requant", "raw32", "stair"):
+                r = routes.route(route_lib, 4, n, h, w, c, m, k, k, s, k // 2, epi, pool)
+                assert r.kernel == "stream" and r.packed, (n, h, w, c, m, k, s, epi, pool)
+    for (h, w, c, m, k) in layers.WIDE_BINARY:
+        assert routes.route(route_lib, 1, 1, h, w, c, m, k, k, 1, k // 2, "thresh1").kernel == "xnor"
+    for bits, n, K, m, kernel in layers.EXTREME_SUMS:
+        assert routes.route(route_lib, bits, n, 1, 1, K, m, 1, 1, 1, 0, "raw32").kernel == kernel
