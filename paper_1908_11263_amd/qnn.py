@@ -172,8 +172,7 @@ def _stream_int(stream):
 
 
 _pack5 = struct.Struct("@5i").pack
-_layer = struct.Struct("@13i")  # x's descriptor, the geometry's, m, the epilogue
-_pack_layer, _unpack_layer = _layer.pack, _layer.unpack
+_pack6 = struct.Struct("@6i").pack
 _pack_epi = struct.Struct("@i4x4P2i").pack
 
 
@@ -226,24 +225,31 @@ _OUT_BITS = {(kind, bits): {EPI_REQUANT: bits, EPI_STAIR: bits, EPI_THRESH1: 1, 
 def _conv_layer(xshape, bits, m, kh, kw, stride, pad, kind):
     """(output shape, x's descriptor, geometry's descriptor) of a convolution.
     The shape is worked out here for every layer that the library accepts; the
-    others, and arguments that are no 13 integers, take the structures and the
-    library's shape query, which accept or refuse them."""
+    others, and arguments that are no plain integers or not as many as they
+    should be, take the structures and the library's shape query, which accept
+    or refuse them."""
     try:
-        if len(stride) != 2 or len(pad) != 2:
-            raise TypeError
-        d = _pack_layer(*xshape, bits, kh, kw, *stride, *pad, m, kind)
-    except (struct.error, TypeError):
-        yshape = out_shape(xshape, bits, m, kh, kw, stride, pad, kind)
-        return yshape, bytes(Tensor(*xshape, bits)), bytes(ConvGeom(kh, kw, stride[0], stride[1], pad[0], pad[1]))
-    n, h, w, c, bits, kh, kw, sh, sw, ph, pw, m, kind = _unpack_layer(d)
-    obits = _OUT_BITS.get((kind, bits))
-    if obits and kh > 0 and kw > 0 and sh > 0 and sw > 0 and ph >= 0 and pw >= 0 and n >= 0 and h > 0 and w > 0:
-        ho = (h + 2 * ph - kh) // sh + 1
-        wo = (w + 2 * pw - kw) // sw + 1
-        # (sizes near the library's limits are the library's to judge)
-        if (ho > 0 and wo > 0 and c > 0 and m > 0 and n * h * w * c < 1 << 40 and n * ho * wo * m < 1 << 40):
-            return (n, ho, wo, m, obits), d, d[20:]
-    return out_shape((n, h, w, c), bits, m, kh, kw, (sh, sw), (ph, pw), kind), d, d[20:]
+        n, h, w, c = xshape
+        sh, sw = stride
+        ph, pw = pad
+        xd = _pack5(n, h, w, c, bits)
+        g = _pack6(kh, kw, sh, sw, ph, pw)
+        obits = _OUT_BITS.get((kind, bits))
+        if obits and kh > 0 and kw > 0 and sh > 0 and sw > 0 and ph >= 0 and pw >= 0:
+            ho = (h + 2 * ph - kh) // sh + 1
+            wo = (w + 2 * pw - kw) // sw + 1
+            size = n * h * w * c
+            out = n * ho * wo * m
+            # (sizes near the library's limits are the library's to judge; a
+            # number of another type would make either product one too)
+            if (ho > 0 and wo > 0 and h > 0 and w > 0 and c > 0 and 0 < m < 1 << 31 and 0 <= size < 1 << 40 and
+                    0 <= out < 1 << 40 and type(n) is int and type(size) is int and type(out) is int and
+                    type(kind) is int):
+                return (n, ho, wo, m, obits), xd, g
+    except (struct.error, TypeError, ValueError, OverflowError):
+        pass
+    yshape = out_shape(xshape, bits, m, kh, kw, stride, pad, kind)
+    return yshape, bytes(Tensor(*xshape, bits)), bytes(ConvGeom(kh, kw, stride[0], stride[1], pad[0], pad[1]))
 
 
 def _new_out(shape, out, x):

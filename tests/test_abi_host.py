@@ -390,8 +390,8 @@ def test_binding_shapes_and_descriptors_agree_with_the_library(q):
     for v in ((1, 2, 3, 4, 8), (1 << 33, 2, 3, 4, 8), (-1, 1 << 31, 0, 4, 1)):
         assert qnn._tensor_bytes(*v) == bytes(qnn.Tensor(*v))
     xs = (3, 9, 8, 7)
-    _, xd, g = qnn._conv_layer(xs, 8, 5, 1, 2, (3, 4), (5, 6), 0)  # (the library reads the first fields)
-    assert xd.startswith(bytes(qnn.Tensor(*xs, 8))) and g.startswith(bytes(qnn.ConvGeom(1, 2, 3, 4, 5, 6)))
+    assert qnn._conv_layer(xs, 8, 5, 1, 2, (3, 4), (5, 6), 0)[1:] == (bytes(qnn.Tensor(*xs, 8)),
+                                                                    bytes(qnn.ConvGeom(1, 2, 3, 4, 5, 6)))
     assert qnn._epi_bytes(2, None, None, None, None, (-3, 1 << 32)) == bytes(qnn.Epi(2, None, None, None, None, -3, 1 << 32))
 
 
