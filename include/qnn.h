@@ -57,7 +57,10 @@
  *   cannot fit return QNN_ERR_UNSUPPORTED.
  * Memory and streams.  Every device pointer is caller-owned device memory and
  *   must be 16-byte aligned (QNN_ERR_ALIGN).  The library allocates no device
- *   memory and keeps no state besides a per-device capability check.  Work is
+ *   memory and keeps no state besides what does not change while a process
+ *   runs: a per-device capability check, and per kernel whether its local
+ *   memory limit was raised and how many workgroups a compute unit holds (per
+ *   thread).  Work is
  *   enqueued asynchronously on `stream` (a hipStream_t; NULL = the null
  *   stream); outputs are valid once the stream has reached that point.
  * Errors.  Every function returns a qnn_status and never aborts.  All argument

@@ -32,15 +32,16 @@
 //
 // Measured on the device, passes one after another, against the tile kernels
 // (and XNOR / popcount at 1 bit): 256 images of 14x14x256 INT-8 codes, 256 3x3
-// filters, 151 -> 38.7 us (1.5 POP/s); INT-1 8x8x256, 256 3x3 filters, batch
-// 1024, 87 -> 20.0 us; 1x1 INT-8 28x28x128 -> 256, batch 256, 65.8 -> 30.7 us;
-// INT-4 56x56x64 -> 128, stride 2, staircase, batch 256, 84.6 -> 49.3 us;
-// 1000x4096 by 4096x1000 INT-8 58 -> 18.5 us.  What bounds it: where K is long,
-// the main loop (a 2x4 wave tile's step of 64 K bytes is 512 clocks of MFMAs;
-// with the fragment reads, slice stores and the barrier the loop runs at
-// 60-70% of the matrix rate with two workgroups per compute unit); where K is
-// short, the chain of a tile's prologue (parameters, pixel offsets, loads,
-// staging) and its compression.
+// filters, 151 -> 39.4 us (1.5 POP/s); INT-1 8x8x256, 256 3x3 filters, batch
+// 1024, 90 -> 20.9 us; 1x1 INT-8 28x28x128 -> 256, batch 256, 65.9 -> 30.9 us;
+// INT-4 56x56x64 -> 128, stride 2, staircase, batch 256, 84.8 -> 49.4 us;
+// 1000x4096 by 4096x1000 INT-8 58 -> 16.6 us.  What bounds it: where K is long,
+// the main loop (the first of these layers keeps the matrix cores busy for 35%
+// of the kernel's SIMD cycles, 45% on the compute units that hold two of its
+// 392 tiles; a wave waits for a third of its time); where K is short, the chain
+// of a tile's prologue (parameters, pixel offsets, loads, staging) and its
+// compression (the 1x1 layer issues vector instructions in 47% of the SIMD
+// cycles and matrix ones in 10%, the strided one in 38% and 12%).
 #pragma once
 
 #include "conv_m32_impl.h"
@@ -161,8 +162,9 @@ enum { STREAM_CODES = 0, STREAM_RAW = 1, STREAM_POOL = 2 };
 // batch 256, 65.4 -> 49.3 us; 8x30x56 -> 16, pooled, batch 12222, 190 -> 125.
 // Where no more workgroups fit it costs up to 7%, except with one-tap filters,
 // whose input is read once: 1x1 56x22x64 -> 34, stride 2, pooled, batch 3005,
-// 28.8 -> 19.9 us, so these are built packed only.  2- and 1-bit codes take more instructions
-// per fragment and feed matrix instructions of half the length: not built.
+// 28.8 -> 19.9 us, so these are built packed only.  2- and 1-bit codes take
+// more instructions per fragment, beside e2m1 matrix instructions of the same 32
+// clocks: not built.
 template <int BITS, int WM, int WN, int WCH, int G, int MODE, int LG, bool TAIL, bool PW, bool XP>
 __global__ void __launch_bounds__(256, (WM * WN >= 6 ? 2 : (WM * WN >= 4 ? 3 : 4))) conv_stream_kernel(StreamArgs a)
 {
@@ -188,9 +190,9 @@ __global__ void __launch_bounds__(256, (WM * WN >= 6 ? 2 : (WM * WN >= 4 ? 3 : 4
     constexpr int UX = PW ? (PT * QPR + 255) / 256 : 4;
     // loads are issued D steps ahead.  One-tap filters wait for both operands
     // in every step: four steps where the tile leaves registers for it (1000
-    // INT-8 images of 4096 codes to 1000 outputs 21.3 -> 18.5 us, 40 drawn
-    // linear layers 0.98; packed 4-bit tiles gained nothing and lost 5% on
-    // reductions of two steps)
+    // INT-8 images of 4096 codes to 1000 outputs 21.3 -> 18.5 us in graph
+    // replays, 40 drawn linear layers 0.98; packed 4-bit tiles gained nothing
+    // and lost 5% on reductions of two steps)
     constexpr int D = PW ? (UX + UW <= 3 && !XP ? 4 : 2) : 3 - G;
     // log2 of the weight scale the accumulator carries (4-bit filters are staged as 16 w)
     constexpr int SL = BITS == 4 ? 4 : 0;

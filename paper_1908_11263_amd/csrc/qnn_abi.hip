@@ -287,9 +287,10 @@ qnn_status plan_conv_mfma(ConvArgs &a, int bits, int &mr, int &nc, int &al16,
     return QNN_OK;
 }
 
-// 32x32x32 kernel with packed filters in LDS: used when the layer has at
-// least 32 output channels and enough tiles for two per compute unit; the
-// preferred tile keeps two workgroups per compute unit in the local memory.
+// 32x32x32 kernel with packed filters in LDS: the tile kernel of layers with at
+// least 32 output channels and enough tiles for two per compute unit (which
+// kernel such a layer then takes, this or the streaming one, run_conv decides);
+// the preferred tile keeps two workgroups per compute unit in the local memory.
 // f4: INT-2 layer on the e2m1 instruction (filter rows staged as 16 bytes of
 // nibbles per 32-deep K chunk, like an 8-bit layer of half the channels).
 qnn_status plan_conv_m32(ConvArgs &a, int bits, int &wm, int &wn, int &al16, int &nw,
@@ -366,8 +367,8 @@ qnn_status plan_conv_m32(ConvArgs &a, int bits, int &wm, int &wn, int &al16, int
             return QNN_OK;
         }
     }
-    // pass 2 (pooled layers and the e2m1 path, which have no other kernel to
-    // fall back on): any tile that fits, even with few tiles
+    // pass 2 (pooled layers and the e2m1 path, which have no other tile kernel):
+    // any tile that fits, even with few tiles
     const bool last_resort = a.pool || f4;
     for (int pass = 0; pass < (last_resort ? 3 : 2); ++pass) {
         const int64_t lds_cap = pass == 0 ? kLdsBytes / 2 : kLdsBytes;
@@ -706,10 +707,13 @@ bool plan_stream(StreamArgs &best, int &variant, const qnn_tensor *x, int32_t m,
         c.mtiles = (int32_t)mtiles;
         c.ptiles = (int32_t)ptiles;
         c.div_mt = make_fastdiv((uint32_t)mtiles);
-        // clocks of the whole grid: a step of one workgroup takes the longest
-        // of its MFMAs, its LDS traffic (128 B per clock) and its loads (about
-        // 32 B per clock and compute unit); a lone workgroup also waits out
-        // the loads' latency, which others on its compute unit cover
+        // A cost that ranks tiles: clocks of the whole grid.  A step of one
+        // workgroup takes the longest of its MFMAs, its LDS traffic (128 B per
+        // clock) and its loads (about 32 B per clock and compute unit); a lone
+        // workgroup also waits out the loads' latency, which others on its
+        // compute unit cover.  The constants were set by hand and it is no
+        // time: over 45,034 random layers the kernel takes 2.3 times as long
+        // (at 2.4 GHz), with a spread of 26%, 20 to 29% at each tile
         const int64_t occ = stream_resident(c, T);
         const int64_t units = mtiles * ptiles;
         const int64_t conc = (units + kPlanCus - 1) / kPlanCus < occ ? (units + kPlanCus - 1) / kPlanCus : occ;
@@ -981,8 +985,13 @@ qnn_status run_conv(const qnn_tensor *x, const void *x_dev, int32_t m, const voi
     // tile.  Its 16x16 tiles read 32 rows of K each, about 10 MB/us in all
     // from the L2s, while the streaming kernel's time goes with its steps
     // along K (about 2 us and 0.25 us per 64 staged bytes): 1000 images of
-    // 4096 INT-8 codes to 1000 outputs, 520 MB, 58 against 18.5 us; 500 images
-    // of 2176 to 93, 13 MB, 4.8 against 12.3 us
+    // 4096 INT-8 codes to 1000 outputs, 520 MB, 58 against 18.5 us (graph
+    // replays); 500 images of 2176 to 93, 13 MB, 4.8 against 12.3 us.  The line
+    // counts packed bytes and was drawn at 8 bits, where 3 of 120 layers of a
+    // grid of sizes are more than 10% faster on the other kernel; at 4 and 2
+    // bits, whose tiles take longer per packed byte, it keeps this kernel too
+    // long (7 and 20 of 120, up to 1.54 and 2.25 times: 4096 images of 256
+    // INT-2 codes to 512 outputs, 11.3 against 5.0 us)
     if (!force && e->kind == QNN_EPI_RAW32 && x->bits != 1 && g->kh == x->h && g->kw == x->w &&
         g->pad_h == 0 && g->pad_w == 0 && K % 64 == 0) {
         st = device_info(&cus);
