@@ -750,7 +750,7 @@ bool stream_weak(const StreamArgs &a, int variant)
     const StreamTile &T = kStreamTiles[variant];
     const int PT = 32 * T.wn * (4 / T.wch);
     return (int64_t)a.ptiles * a.mtiles <= kPlanCus || stream_resident(a, T) <= 1 ||
-           (!a.pw1 && a.nslots >= (int64_t)4 * PT * a.ssh * a.ssw);
+           (!a.pw1 && a.nslots >= 4.0 * PT * a.ssh * a.ssw);  // (strides may be near 2^31)
 }
 
 // Predicted microseconds of both kernels, for layers where stream_weak holds.
