@@ -89,8 +89,14 @@ qnn_status check_tensor(const qnn_tensor *t)
 {
     if (t->n < 0 || t->h < 1 || t->w < 1 || t->c < 1)
         return QNN_ERR_SHAPE;
-    if ((int64_t)t->n * t->h * t->w * pixel_bytes64(t) > ((int64_t)1 << 40))
-        return QNN_ERR_SHAPE;
+    // (factor by factor: the product of four may pass 64 bits)
+    constexpr int64_t most = (int64_t)1 << 40;
+    int64_t bytes = t->n;
+    for (const int64_t f : {(int64_t)t->h, (int64_t)t->w, pixel_bytes64(t)}) {
+        if (bytes > most / f)
+            return QNN_ERR_SHAPE;
+        bytes *= f;
+    }
     return QNN_OK;
 }
 

@@ -447,3 +447,22 @@ def test_binding_refuses_strides_and_pads_of_another_length(q):
         for f in (q.conv2d, q.conv2d_maxpool):
             with pytest.raises((TypeError, IndexError)):
                 f(x, (1, 4, 4, 32), 8, x, 8, 3, 3, stride, pad, "requant", mult=x, shift=x, stream=HostStream())
+
+
+def test_sizes_past_64_bits_are_refused(q, L):
+    """Descriptors whose byte count wraps around to a small one."""
+    from paper_1908_11263_amd import qnn
+    g = qnn.ConvGeom(1, 1, 1, 1, 0, 0)
+    for n, h, w, c in ((1 << 30, 1 << 30, 16, 4), (1 << 22, 1 << 22, 1 << 18, 4), (1 << 30, 1 << 30, 1 << 30, 1 << 30),
+                       (3, 1 << 30, 1 << 30, 1 << 30)):
+        y = qnn.Tensor()
+        assert L.qnn_conv2d_out_shape(ctypes.byref(qnn.Tensor(n, h, w, c, 8)), 8, ctypes.byref(g), 2, ctypes.byref(y)) == 3
+        with pytest.raises(q.QnnError) as e:
+            qnn.out_shape((n, h, w, c), 8, 8, 1, 1)
+        assert e.value.status == 3
+    # as many bytes as there may be, and none
+    y = qnn.Tensor()
+    assert L.qnn_conv2d_out_shape(ctypes.byref(qnn.Tensor(1 << 10, 1 << 10, 1 << 10, 1 << 10, 8)), 8, ctypes.byref(g), 2,
+                                  ctypes.byref(y)) == 0
+    assert L.qnn_conv2d_out_shape(ctypes.byref(qnn.Tensor(0, 1 << 30, 1 << 30, 1 << 30, 8)), 8, ctypes.byref(g), 2,
+                                  ctypes.byref(y)) == 0
